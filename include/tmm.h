@@ -189,8 +189,13 @@ int tmm_year_adjoint(tmm_handle h, const double *y0, const double *obs, int ckpt
 
 /* Options (tmm_set_option). */
 enum {
-    TMM_OPT_PERSISTENT = 1,  /* 1 (default): single-member model years run as one persistent
-                                cooperative launch when the grid fits; 0: one launch per step */
+    TMM_OPT_PERSISTENT = 1,  /* 1 (default): model years run as one persistent cooperative launch
+                                when the grid fits: a single member's always, a batch's in groups of
+                                as many members as fit the device side by side where that is faster
+                                than one launch per step for all of them (few groups; tangents,
+                                gradients and three tracers always) and neither
+                                TMM_OPT_MEMBER_KERNEL_MIN nor TMM_OPT_MEMBER_TILE asks for another
+                                kernel; 0: one launch per step */
     TMM_OPT_DOMAIN_ROWS = 2, /* target rows per workgroup of the persistent kernel (<= 512);
                                 0 = the default (256) */
     TMM_OPT_MEMBER_KERNEL_MIN = 3, /* forward steps of batches with at least this many members use the
@@ -217,12 +222,14 @@ enum {
                                     kernels: 32, 64, 128 or 256 (a tiling no deeper than the
                                     deepest column is used as the smallest); 0 = by state width
                                     (128 up to 4 state columns, else 256) */
-    TMM_OPT_WAVE_LOCAL = 10,     /* 1 (default): the persistent forward kernels place each water
-                                    column within one wavefront where the domains allow it (more,
-                                    smaller domains if needed), so that a time step needs one
-                                    workgroup barrier instead of three; 0: packed columns and
-                                    three barriers per step.  Rebuilds the domains; the results
-                                    are the same bit for bit */
+    TMM_OPT_WAVE_LOCAL = 10,     /* 1 (default): the persistent kernels place each water column
+                                    within 16 or 32 lanes of a wavefront (at most 32 layers, 5
+                                    explicit entries per row, 256 rows per domain, and a domain for
+                                    every compute unit at most), else within one wavefront, where
+                                    the domains allow it (more, smaller domains if needed), so that
+                                    a time step needs one workgroup barrier instead of three; 0:
+                                    packed columns and three barriers per step.  Rebuilds the
+                                    domains; the forward results are the same bit for bit */
     TMM_OPT_MEMBER_TILE = 11,    /* 0 (default): member-parallel steps of two-tracer models use one
                                     wavefront per water column that reads its stencil's state rows
                                     itself; 4 or 8: workgroups of that many neighbouring columns

@@ -18,6 +18,7 @@
 #include "tmm.h"
 #include "tmm_device.hpp"
 #include "tmm_persistent.hpp"
+#include "tmm_bins.hpp"
 #include "tmm_probe.hpp"
 
 // Scratch of tmm_year_noalloc: a fixed device array instead of workspace or
@@ -134,18 +135,23 @@ struct Plan {
     size_t o_finite;                // set by the per-year non-finite check
     size_t o_probe;                 // words, results and load chain of tmm_probe_exchange
     size_t o_ring, o_vring;         // state rings of the persistent forward kernel (0: none)
+    int pers_members;               // members they hold
     size_t o_phaloptr, o_phalo;     // halo rows of each domain
     size_t o_pqlat;                 // latitude rows of each domain (insolation table in LDS)
     size_t o_pcolslot;              // first slot (thread) of each water column in its domain
     size_t o_pahaloptr, o_pahalo;   // ... for the transposed stencil (reverse sweep)
+    bool bins_possible;             // stencil and columns of the binned layout's kernels
+    size_t o_blane, o_bae, o_baet, o_bcell;   // lanes, LDS cells and ring rows of the binned layout (0: none)
     size_t dep_capacity, halo_capacity;
     size_t total;
 };
 
 constexpr int kMaxDomains = 4096;
+constexpr int kMaxBinDomains = 1024;        // domains of the binned layout (one per compute unit at most)
 // grids up to this many rows get the persistent kernel's state rings
 // (2 x kRing x n x ntr doubles); larger ones cannot be resident anyway
 constexpr int kMaxPersistentRows = 256 * tmm::kPersistThreadsMax;
+constexpr int kMemberRingRows = 65536;      // rows over all members of one launch (sizes the rings)
 constexpr int kDefaultDomainRows = 256;     // rows per persistent workgroup unless set by option (tuned on MI355X)
 constexpr int kMembersWavesMax = 8;         // wavefronts per workgroup of the member kernel, at most
 constexpr int kDefaultBandRows = 16;        // latitude rows per band of the member kernel's column order
@@ -279,8 +285,8 @@ int validate(const tmm_desc* d, Plan& P) {
         P.o_final = take(astate);
         P.o_mu[0] = take(astate);
         P.o_mu[1] = take(astate);
-        P.o_pubar = take((size_t)kMaxDomains * 8 * 8);
-        P.o_pjpart = take(nm * kMaxDomains * 8);
+        P.o_pubar = take((size_t)kMaxDomains * P.adj_nb * P.nparam * 8);
+        P.o_pjpart = take(nm * kMaxDomains * P.adj_nb * 8);
     } else {
         P.o_pubar = P.o_pjpart = 0;
         P.o_ubt = P.o_jpart = P.o_ckpt = P.o_seg = P.o_final = P.o_mu[0] = P.o_mu[1] = 0;
@@ -315,7 +321,7 @@ int validate(const tmm_desc* d, Plan& P) {
     P.o_pdomcol = take((size_t)(kMaxDomains + 1) * 4);
     P.o_pdepptr = take((size_t)(kMaxDomains + 1) * 4);
     P.o_pdepidx = take(P.dep_capacity * 4);
-    P.o_pflags = take((size_t)kMaxDomains * 4);
+    P.o_pflags = take((size_t)kMaxDomains * 4);     // domains x members of a launch
     P.o_pabort = take(64);
     P.o_finite = take(64);
     P.o_probe = take(kProbeBytes);
@@ -326,10 +332,22 @@ int validate(const tmm_desc* d, Plan& P) {
     P.o_pahalo = take(P.halo_capacity * 4);
     P.o_pqlat = take((size_t)kMaxDomains * (1 + tmm::kInsLat) * 4);
     P.o_pcolslot = take((size_t)d->ncol * 4);
+    P.bins_possible = d->n <= kMaxPersistentRows && P.ew <= tmm::kBinEll && P.etw <= tmm::kBinEll && d->nlayer <= 32;
     if (d->n <= kMaxPersistentRows) {
-        P.o_ring = take((size_t)tmm::kRing * d->n * P.ntr * 8);
-        P.o_vring = take((size_t)tmm::kRing * d->n * P.ntr * 8);
+        P.o_blane = take((size_t)kMaxBinDomains * tmm::kBinThreads * 16);
+        P.o_bae = take((size_t)tmm::kBinEll * npad * 4);
+        P.o_baet = take((size_t)tmm::kBinEll * npad * 4);
+        P.o_bcell = take(npad * 4);
     } else {
+        P.o_blane = P.o_bae = P.o_baet = P.o_bcell = 0;
+    }
+    if (d->n <= kMaxPersistentRows) {
+        // rings for the members that one launch may run side by side
+        P.pers_members = std::min(d->nbatch_max, std::max(1, kMemberRingRows / d->n));
+        P.o_ring = take((size_t)P.pers_members * tmm::kRing * npad * P.ntr * 8);
+        P.o_vring = take((size_t)P.pers_members * tmm::kRing * npad * P.ntr * 8);
+    } else {
+        P.pers_members = 0;
         P.o_ring = P.o_vring = 0;
     }
     P.total = o;
@@ -353,6 +371,8 @@ struct tmm_ctx {
     bool pers_enabled = true;      // option TMM_OPT_PERSISTENT
     long long spin_limit = 1ll << 22;   // option TMM_OPT_SPIN_LIMIT
     int pers_G = 0;
+    int pers_M = 1;                // members one launch runs side by side
+    int bins = 0;                  // 16-lane rows per bin of the binned layout (0: the layout of tmm_persistent.hpp)
     int pers_kmax = 16;
     int pers_tpb = 256;            // threads (= maximum rows) per domain
     int pers_hmax = 0;             // largest domain halo (rows)
@@ -373,7 +393,8 @@ struct tmm_ctx {
     int mem_blocks_p[2] = {0, 0};  // workgroups of the packed member kernels (32, 16 members per column)
     int mem_tile = 0;              // option TMM_OPT_MEMBER_TILE: columns per workgroup of the tiled
                                    // member kernel (0: k_step_members)
-    std::vector<int> ell_col;      // Ae's ELL columns [ew][npad] (host copy, for the tile tables)
+    std::vector<int> ell_col;      // Ae's ELL columns [ew][npad] (host copy, for the tile and bin tables)
+    std::vector<int> ellt_col;     // Ae^T's [etw][npad]
     // captured model years of the launch-per-step path, keyed by their arguments
     struct YearGraph {
         int nb;
@@ -817,76 +838,191 @@ tmm::Persist persist_args(tmm_ctx* h) {
     ps.qlat_max = h->pers_qmax;
     ps.col_slot = h->at<int>(P.o_pcolslot);
     ps.wave_local = h->pers_wave_local ? 1 : 0;
+    ps.ring_len = (size_t)tmm::kRing * P.npad * P.ntr;
     return ps;
 }
 
-int reset_flags(tmm_ctx* h) {
-    hipLaunchKernelGGL(tmm::k_fill_int, dim3((h->pers_G + 255) / 256), dim3(256), 0, h->stream,
-                       h->at<int>(h->P.o_pflags), h->pers_G, 0);
+// A state as one launch's members see it: the row-major batch of W columns
+// from slot slot0 on, or compact states (n x ntr), `step` doubles apart.
+tmm::StateView batch_view(const tmm_ctx* h, const double* p, int W, int slot0) {
+    const int ntr = h->P.ntr;
+    return tmm::StateView{const_cast<double*>(p) + (p ? (size_t)slot0 * ntr : 0), W, (size_t)ntr};
+}
+tmm::StateView compact_view(const tmm_ctx* h, const double* p, size_t step) {
+    return tmm::StateView{const_cast<double*>(p), h->P.ntr, step};
+}
+
+const void* bins_year_kernel(const tmm_ctx* h, bool tangent, bool ql) {
+    const bool sub = h->P.nsub > 1;
+    return h->P.ntr == 3 ? tmm::bins_year_kernel_3(tangent, sub, ql, h->bins)
+         : h->P.ntr == 2 ? tmm::bins_year_kernel_2(tangent, sub, ql, h->bins)
+                         : tmm::bins_year_kernel_1(tangent, sub, ql, h->bins);
+}
+
+const void* bins_adjoint_kernel(const tmm_ctx* h) {
+    const bool sub = h->P.nsub > 1;
+    return h->P.ntr == 3 ? tmm::bins_adjoint_kernel_3(sub, h->bins)
+         : h->P.ntr == 2 ? tmm::bins_adjoint_kernel_2(sub, h->bins)
+                         : tmm::bins_adjoint_kernel_1(sub, h->bins);
+}
+
+// Pause before the first poll of a step (64-cycle units, see hold_poll), the
+// measured optimum of the three kernels by the work a step does before it:
+// none where internal BGC steps already take longer than a value needs to
+// arrive; less in 32-lane bins (twice the product) and on few domains (a store
+// is seen sooner).  Model year on the 128x64x15 grid, ms at 0 / 5 / 7 / 9 / 12:
+// PO4-DOP 4.35 / 3.85 / 3.64 / 3.73 / 3.92, PO4-DOP-PHY 6.30 / 5.62 / 5.28 /
+// 5.10 / 5.18; its tangent year 6.02 / 5.60 / 5.53 / 5.56 / 5.67; on the
+// 32x16x8 grid (12 domains) 3.22 at 0, 3.08 at 2, 3.32 at 7.
+int poll_hold(const tmm_ctx* h, bool tangent, bool reverse) {
+    if (h->P.nsub > 1) return 0;
+    const bool few = h->pers_G * h->pers_M < 64;
+    if (reverse) return few ? 1 : (h->bins == 2 ? 2 : 6);
+    if (tangent) return few ? 0 : (h->bins == 2 ? 2 : 6);
+    const int base = h->P.ntr == 3 ? 9 : 7;
+    return few ? 3 : (h->bins == 2 ? base - 3 : base);
+}
+
+tmm::Bins bins_args(const tmm_ctx* h, bool tangent, bool reverse) {
+    const Plan& P = h->P;
+    tmm::Bins b;
+    b.hold = poll_hold(h, tangent, reverse);
+    b.lane = h->at<int4>(P.o_blane);
+    b.ae_lds = h->at<int>(P.o_bae);
+    b.aet_lds = h->at<int>(P.o_baet);
+    b.halo_ptr = h->at<int>(P.o_phaloptr);
+    b.halo_cell = h->at<int>(P.o_phalo);
+    b.ahalo_ptr = h->at<int>(P.o_pahaloptr);
+    b.ahalo_cell = h->at<int>(P.o_pahalo);
+    b.halo_max = h->pers_hmax;
+    b.ahalo_max = h->pers_ahmax;
+    b.cells = P.npad;
+    return b;
+}
+
+// Ring slot 0 = the initial state, slots 1 .. K-1 the sentinel.
+int init_rings(tmm_ctx* h, int M, size_t ring, tmm::StateView y) {
+    const Plan& P = h->P;
+    const size_t ring_len = (size_t)tmm::kRing * P.npad * P.ntr;
+    if (h->bins) {
+        const size_t total = (size_t)tmm::kRingK * P.npad * P.ntr;   // slots 0 .. K-1
+        hipLaunchKernelGGL(tmm::k_bins_ring_init, dim3(launch_blocks(total), M), dim3(256), 0, h->stream,
+                           h->at<double>(ring), ring_len, y, P.ntr, P.npad, h->at<int>(P.o_bcell), total);
+    } else {
+        const size_t total = (size_t)tmm::kRingK * P.n * P.ntr;
+        hipLaunchKernelGGL(tmm::k_ring_init, dim3(launch_blocks(total), M), dim3(256), 0, h->stream,
+                           h->at<double>(ring), ring_len, y, P.n, P.ntr, total);
+    }
     TMM_LAUNCHED();
     return TMM_OK;
 }
 
-// Steps sr.j0 .. sr.j1-1 in one cooperative launch (one member).
-int launch_persistent(tmm_ctx* h, tmm::StepRange sr, const double* y, double* out, const double* v = nullptr,
-                      double* vout = nullptr) {
-    const Plan& P = h->P;
-    int rc = reset_flags(h);
-    if (rc) return rc;
-    // ring slot 0 = the initial state, the others the sentinel
-    const size_t slen = (size_t)P.n * P.ntr, ring_len = (size_t)tmm::kRingK * slen;   // slots 0 .. K-1
-    hipLaunchKernelGGL(tmm::k_ring_init, dim3(launch_blocks(ring_len)), dim3(256), 0, h->stream,
-                       h->at<double>(P.o_ring), y, P.n, P.ntr, ring_len);
+int reset_flags(tmm_ctx* h, int M) {
+    const int nf = M * h->pers_G;
+    hipLaunchKernelGGL(tmm::k_fill_int, dim3((nf + 255) / 256), dim3(256), 0, h->stream, h->at<int>(h->P.o_pflags), nf,
+                       0);
     TMM_LAUNCHED();
-    if (v) {
-        hipLaunchKernelGGL(tmm::k_ring_init, dim3(launch_blocks(ring_len)), dim3(256), 0, h->stream,
-                           h->at<double>(P.o_vring), v, P.n, P.ntr, ring_len);
-        TMM_LAUNCHED();
-    }
+    return TMM_OK;
+}
+
+// Steps sr.j0 .. sr.j1-1 of the members in slots slot0 .. slot0 + M - 1 in
+// one cooperative launch.
+int launch_persistent(tmm_ctx* h, int M, int slot0, tmm::StepRange sr, tmm::StateView y, tmm::StateView out,
+                      tmm::StateView v = {}, tmm::StateView vout = {}) {
+    const Plan& P = h->P;
+    int rc = reset_flags(h, M);
+    if (rc || (rc = init_rings(h, M, P.o_ring, y)) || (v.p && (rc = init_rings(h, M, P.o_vring, v)))) return rc;
     tmm::Grid g = h->grid(h->tilings.front());
     tmm::Model md = h->model();
     tmm::Mats mt = h->mats();
     tmm::Persist ps = persist_args(h);
     double dtd = tmm::kDaysPerYear / P.nstep;
-    void* args[] = {&g, &md, &mt, &ps, &sr, &dtd, &y, &out, &v, &vout};
-    const bool ql = h->pers_ql[v != nullptr ? 1 : 0];
-    TMM_TRY(hipLaunchCooperativeKernel(persistent_kernel(P.ntr, v != nullptr, h->pers_kmax, h->pers_tpb, persistent_sn(P),
-                                                         ql),
-                                       dim3(h->pers_G), dim3(h->pers_tpb), args,
-                                       tmm::year_kernel_dyn_lds(h->pers_tpb, h->pers_hmax, P.ntr, v != nullptr,
+    const bool tangent = v.p != nullptr;
+    const bool ql = h->pers_ql[tangent ? 1 : 0];
+    if (h->bins) {
+        tmm::Bins bn = bins_args(h, tangent, false);
+        void* args[] = {&g, &md, &mt, &ps, &bn, &sr, &dtd, &slot0, &y, &out, &v, &vout};
+        TMM_TRY(hipLaunchCooperativeKernel(bins_year_kernel(h, tangent, ql), dim3(h->pers_G, M),
+                                           dim3(tmm::kBinThreads), args,
+                                           tmm::bins_year_lds(h->pers_hmax, P.ntr, tangent), h->stream));
+        h->pers_used = true;
+        return TMM_OK;
+    }
+    void* args[] = {&g, &md, &mt, &ps, &sr, &dtd, &slot0, &y, &out, &v, &vout};
+    TMM_TRY(hipLaunchCooperativeKernel(persistent_kernel(P.ntr, tangent, h->pers_kmax, h->pers_tpb, persistent_sn(P), ql),
+                                       dim3(h->pers_G, M), dim3(h->pers_tpb), args,
+                                       tmm::year_kernel_dyn_lds(h->pers_tpb, h->pers_hmax, P.ntr, tangent,
                                                                 ql ? h->pers_qmax : 0, P.nstep),
                                        h->stream));
     h->pers_used = true;
     return TMM_OK;
 }
 
-int launch_persistent_year(tmm_ctx* h, const double* y, double* out, const double* v, double* vout) {
-    tmm::StepRange sr{0, h->P.nstep, nullptr, 1, nullptr, nullptr};
-    return launch_persistent(h, sr, y, out, v, vout);
+// A model year of nb slots, as many at a time as fit the device side by side.
+int launch_persistent_year(tmm_ctx* h, int nb, const double* y, double* out, const double* v, double* vout) {
+    const int W = nb * h->P.ntr;
+    tmm::StepRange sr{0, h->P.nstep, nullptr, 1, 0, {}, 0, nullptr, 1};
+    for (int s = 0; s < nb; s += h->pers_M) {
+        const int M = std::min(h->pers_M, nb - s);
+        const int rc = launch_persistent(h, M, s, sr, batch_view(h, y, W, s), batch_view(h, out, W, s),
+                                         batch_view(h, v, W, s), batch_view(h, vout, W, s));
+        if (rc) return rc;
+    }
+    return TMM_OK;
 }
 
-// Reverse sweep over steps j_hi-1 .. j_lo in one cooperative launch.
-int launch_adjoint_persistent(tmm_ctx* h, int j_lo, int j_hi, const double* ystore, const double* obs,
-                              double src_scale, const double* mu_in, double* mu_out, double* ubar_dom) {
+// Reverse sweep over steps j_hi-1 .. j_lo of the members in slots slot0 ..
+// slot0 + M - 1 in one cooperative launch; ystore and obs are those slots'.
+int launch_adjoint_persistent(tmm_ctx* h, int M, int slot0, int j_lo, int j_hi, const double* ystore,
+                              size_t ystore_step, tmm::StateView obs, size_t obs_month, double src_scale,
+                              tmm::StateView mu_in, tmm::StateView mu_out, double* ubar_dom, int ubar_ld) {
     const Plan& P = h->P;
-    int rc = reset_flags(h);
-    if (rc) return rc;
     // the cotangent uses the forward kernel's ring (launches never overlap)
-    const size_t slen = (size_t)P.n * P.ntr, ring_len = (size_t)tmm::kRingK * slen;   // slots 0 .. K-1
-    hipLaunchKernelGGL(tmm::k_ring_init, dim3(launch_blocks(ring_len)), dim3(256), 0, h->stream,
-                       h->at<double>(P.o_ring), mu_in, P.n, P.ntr, ring_len);
-    TMM_LAUNCHED();
+    int rc = reset_flags(h, M);
+    if (rc || (rc = init_rings(h, M, P.o_ring, mu_in))) return rc;
     tmm::Grid g = h->grid(h->tilings.front());
     tmm::Model md = h->model();
     tmm::Mats mt = h->mats();
     tmm::Persist ps = persist_args(h);
     double dtd = tmm::kDaysPerYear / P.nstep;
-    void* args[] = {&g, &md, &mt, &ps, &dtd, &j_lo, &j_hi, &ystore, &obs, &src_scale, &mu_in, &mu_out, &ubar_dom};
+    if (h->bins) {
+        tmm::Bins bn = bins_args(h, false, true);
+        void* args[] = {&g, &md, &mt, &ps, &bn, &dtd, &slot0, &j_lo, &j_hi, &ystore, &ystore_step, &obs, &obs_month,
+                        &src_scale, &mu_in, &mu_out, &ubar_dom, &ubar_ld};
+        TMM_TRY(hipLaunchCooperativeKernel(bins_adjoint_kernel(h), dim3(h->pers_G, M), dim3(tmm::kBinThreads), args,
+                                           tmm::bins_adjoint_lds(h->pers_ahmax, P.ntr, P.nsub > 1 ? P.nsub : 0),
+                                           h->stream));
+        h->pers_used = true;
+        return TMM_OK;
+    }
+    void* args[] = {&g, &md, &mt, &ps, &dtd, &slot0, &j_lo, &j_hi, &ystore, &ystore_step, &obs, &obs_month, &src_scale,
+                    &mu_in, &mu_out, &ubar_dom, &ubar_ld};
     TMM_TRY(hipLaunchCooperativeKernel(adjoint_kernel(P.ntr, h->pers_kmax, h->pers_tpb, persistent_sn(P)),
-                                       dim3(h->pers_G), dim3(h->pers_tpb), args,
+                                       dim3(h->pers_G, M), dim3(h->pers_tpb), args,
                                        adjoint_dyn_lds(P, h->pers_tpb, h->pers_ahmax), h->stream));
     h->pers_used = true;
     return TMM_OK;
+}
+
+// Whether nb members' model years run through the single-launch kernels, as
+// many members at a time as fit the device, one group after another, instead
+// of one launch per step for the whole batch.  A group's year takes 3.1-3.9 ms
+// (two tracers) whatever the grid; the member kernel's year, at 8 / 32 / 64
+// members, 44 / 60 / 92 ms on the 128x64x15 grid (one member per group), 26 /
+// 33 / 44 ms on 77x39x12 (17000 points, 3 per group) and 22 / 20 / 25 ms on
+// 32x16x8 (2700 points, 21 per group).  The other layout's year is up to twice
+// as long.  Three tracers and derivatives have only the tile kernels besides,
+// whose time grows with the member count (6 members of PO4-DOP-PHY on the
+// 128x64x15 grid 147 ms, a group 5.1 ms).
+bool single_launch(const tmm_ctx* h, int nb, bool derivative) {
+    if (!h->pers_ok || !h->pers_enabled) return false;
+    if (nb == 1) return true;
+    // a launch-per-step kernel asked for by its options runs
+    if (h->wide_min_members >= 0 || h->mem_tile > 0) return false;
+    const bool members = h->P.ntr <= 2 && h->P.nlayer <= 32 && h->P.ew <= tmm::kMembersEll;
+    if (derivative || !members) return true;
+    const int groups = (nb + h->pers_M - 1) / h->pers_M;
+    return groups <= (h->bins ? 6 + h->P.n / 10000 : 4);
 }
 
 // After the persistent launches of a call: a set abort flag means a wait
@@ -971,11 +1107,11 @@ int run_year_graph(tmm_ctx* h, int nb, const double* y, double* out, double* a, 
 
 // One model year for nb slots from y to out, ping-ponging through a, b.  The
 // last step writes out directly.  Tangent when v != nullptr (vout, va, vb).
-// One member on a handle with the persistent tables runs as one persistent
-// launch; otherwise one launch per step.
+// As persistent launches where single_launch() says so, else one launch per
+// step.
 int run_year(tmm_ctx* h, int nb, const double* y, double* out, double* a, double* b,
              const double* v = nullptr, double* vout = nullptr, double* va = nullptr, double* vb = nullptr) {
-    if (nb == 1 && h->pers_ok && h->pers_enabled) return launch_persistent_year(h, y, out, v, vout);
+    if (single_launch(h, nb, v != nullptr)) return launch_persistent_year(h, nb, y, out, v, vout);
     if (!v && h->graphs_enabled) return run_year_graph(h, nb, y, out, a, b);
     const double* cur = y;
     const double* vcur = v;
@@ -1007,6 +1143,285 @@ int ensure_dyn_lds(const void* fk, size_t dyn) {
     return TMM_OK;
 }
 
+// Domains that share an explicit-matrix coupling (either direction) with each
+// domain: the ones it hands over with.
+void domain_deps(const tmm_ctx* h, const std::vector<int>& row_dom, int G, std::vector<int>& ptr, std::vector<int>& idx) {
+    std::vector<std::vector<int>> deps(G);
+    for (int i = 0; i < h->P.n; ++i)
+        for (int e = h->ae_rowptr[i]; e < h->ae_rowptr[i + 1]; ++e) {
+            const int a = row_dom[i], b = row_dom[h->ae_colidx[e]];
+            if (a != b) {
+                deps[a].push_back(b);
+                deps[b].push_back(a);
+            }
+        }
+    ptr.assign(G + 1, 0);
+    idx.clear();
+    for (int q = 0; q < G; ++q) {
+        std::sort(deps[q].begin(), deps[q].end());
+        deps[q].erase(std::unique(deps[q].begin(), deps[q].end()), deps[q].end());
+        idx.insert(idx.end(), deps[q].begin(), deps[q].end());
+        ptr[q + 1] = (int)idx.size();
+    }
+}
+
+// Halo of each domain: what its rows read of other domains, as where[row],
+// ascending.  transposed: row i of Ae^T reads the rows whose Ae rows have an
+// entry in column i.  Returns the largest.
+int domain_halos(const tmm_ctx* h, const std::vector<int>& row_dom, const std::vector<int>& where, int G,
+                 bool transposed, std::vector<int>& ptr, std::vector<int>& halo) {
+    std::vector<std::vector<int>> hq(G);
+    for (int i = 0; i < h->P.n; ++i)
+        for (int e = h->ae_rowptr[i]; e < h->ae_rowptr[i + 1]; ++e) {
+            const int reader = transposed ? h->ae_colidx[e] : i, read = transposed ? i : h->ae_colidx[e];
+            if (row_dom[reader] != row_dom[read]) hq[row_dom[reader]].push_back(where[read]);
+        }
+    int most = 0;
+    ptr.assign(G + 1, 0);
+    halo.clear();
+    for (int q = 0; q < G; ++q) {
+        std::sort(hq[q].begin(), hq[q].end());
+        hq[q].erase(std::unique(hq[q].begin(), hq[q].end()), hq[q].end());
+        most = std::max(most, (int)hq[q].size());
+        halo.insert(halo.end(), hq[q].begin(), hq[q].end());
+        ptr[q + 1] = (int)halo.size();
+    }
+    return most;
+}
+
+// Latitude rows of each domain's columns (insolation table in LDS); the most
+// of any domain, or -1 where one spans more than kInsLat.
+int domain_latitudes(const Plan& P, const std::vector<std::vector<int>>& dom_cols, std::vector<int>& qlat) {
+    const int G = (int)dom_cols.size();
+    qlat.assign((size_t)G * (1 + tmm::kInsLat), 0);
+    int qmax = 0;
+    for (int q = 0; q < G; ++q) {
+        int* e = qlat.data() + (size_t)q * (1 + tmm::kInsLat);
+        for (int c : dom_cols[q]) {
+            const int l = P.col_lat[c];
+            if (std::find(e + 1, e + 1 + e[0], l) != e + 1 + e[0]) continue;
+            if (e[0] == tmm::kInsLat) return -1;
+            e[1 + e[0]++] = l;
+        }
+        qmax = std::max(qmax, e[0]);
+    }
+    return qmax;
+}
+
+// Workgroup -> domain: consecutive domains on the same XCD, assuming the
+// round-robin dispatch of workgroups over the 8 XCDs.
+std::vector<int> xcd_order(int G) {
+    std::vector<int> block_dom(G);
+    int next = 0;
+    for (int x = 0; x < 8; ++x)
+        for (int b = x; b < G; b += 8) block_dom[b] = next++;
+    return block_dom;
+}
+
+// The binned layout (tmm_bins.hpp).  Domains are filled along a sweep of the
+// grid in bands of a few latitude rows (longitude by longitude, so that a
+// domain is a compact patch), each column going to the bin with the least
+// room that still holds it.  When the next column of the sweep needs a bin
+// more than the domain has, the room left in its bins goes to shallow columns
+// among the next ones of the sweep.  A few band heights are tried, four rows
+// first, until the domains fit the device.  Sets h->bins where everything fits, else leaves
+// the handle to the layout of tmm_persistent.hpp.
+int build_bins(tmm_ctx* h, int target_rows, int ncu) {
+    const Plan& P = h->P;
+    const int hb = P.nlayer <= 16 ? 1 : 2, BL = 16 * hb, TPB = tmm::kBinThreads;
+    int nbin = std::max(1, std::min(TPB / BL, (target_rows + BL - 1) / BL));
+    struct Layout {
+        std::vector<std::vector<int>> cols, slots;     // per domain: columns and their first lanes
+    };
+    auto depth = [&](int c) { return P.col_start[c + 1] - P.col_start[c]; };
+    auto fill = [&](int band) {
+        std::vector<int> order(P.ncol);
+        for (int c = 0; c < P.ncol; ++c) order[c] = c;
+        if (!P.lon.empty())
+            std::stable_sort(order.begin(), order.end(), [&](int a, int b) {
+                const int ba = P.col_lat[a] / band, bb = P.col_lat[b] / band;
+                if (ba != bb) return ba < bb;
+                if (P.lon[a] != P.lon[b]) return (P.lon[a] < P.lon[b]) == (ba % 2 == 0);
+                return P.col_lat[a] < P.col_lat[b];
+            });
+        Layout out;
+        const int window = 3 * nbin;
+        std::vector<char> used(P.ncol, 0);
+        int first = 0;                                 // first position of the sweep not taken
+        while (first < P.ncol) {
+            std::vector<int> room, cols, slots, lats;
+            auto put = [&](int c, bool open) {
+                // a domain (the first one once half full) keeps to the latitude rows its insolation
+                // table holds
+                const bool known = std::find(lats.begin(), lats.end(), P.col_lat[c]) != lats.end();
+                if (!known && lats.size() == tmm::kInsLat && (!out.cols.empty() || 2 * (int)room.size() >= nbin)) return false;
+                int best = -1;
+                for (int b = 0; b < (int)room.size(); ++b)
+                    if (room[b] >= depth(c) && (best < 0 || room[b] < room[best])) best = b;
+                if (best < 0) {
+                    if (!open || (int)room.size() == nbin) return false;
+                    best = (int)room.size();
+                    room.push_back(BL);
+                }
+                if (!known) lats.push_back(P.col_lat[c]);
+                cols.push_back(c);
+                slots.push_back(best * BL + BL - room[best]);
+                room[best] -= depth(c);
+                used[c] = 1;
+                return true;
+            };
+            int i = first;
+            for (; i < P.ncol; ++i)
+                if (!used[order[i]] && !put(order[i], true)) break;
+            for (int seen = 0; i < P.ncol && seen < window; ++i)
+                if (!used[order[i]]) {
+                    ++seen;
+                    put(order[i], false);
+                }
+            while (first < P.ncol && used[order[first]]) ++first;
+            out.cols.push_back(cols);
+            out.slots.push_back(slots);
+        }
+        return out;
+    };
+    Layout lay;
+    for (;; ++nbin) {                                  // (larger domains than asked for where they are too many)
+        lay = Layout();
+        for (int band : {4, 3, 5}) {
+            Layout l = fill(band);
+            if (lay.cols.empty() || l.cols.size() < lay.cols.size()) lay = std::move(l);
+            if (P.lon.empty() || (int)lay.cols.size() <= std::min(ncu, kMaxBinDomains)) break;
+        }
+        if ((int)lay.cols.size() <= std::min(ncu, kMaxBinDomains)) break;
+        if (nbin == TPB / BL) return TMM_OK;
+    }
+    const int G = (int)lay.cols.size();
+    std::vector<int> row_dom(P.n), row_lane(P.n), row_cell(P.n, 0), cell_row(P.npad, -1);
+    std::vector<int4> lane((size_t)G * TPB, int4{-1, 0, 0, 0});
+    for (int q = 0; q < G; ++q) {
+        for (size_t i = 0; i < lay.cols[q].size(); ++i) {
+            const int c = lay.cols[q][i];
+            for (int k = 0; k < depth(c); ++k) lane[(size_t)q * TPB + lay.slots[q][i] + k] = int4{P.col_start[c] + k, c, 0, 0};
+        }
+        for (int t = 0; t < TPB; ++t) {
+            const int r = lane[(size_t)q * TPB + t].x;
+            if (r < 0) continue;
+            row_dom[r] = q;
+            row_lane[r] = t;
+        }
+    }
+    for (int i = 0; i < P.n; ++i)
+        for (int e = h->ae_rowptr[i]; e < h->ae_rowptr[i + 1]; ++e) {
+            const int j = h->ae_colidx[e];
+            if (row_dom[i] == row_dom[j]) continue;
+            lane[(size_t)row_dom[j] * TPB + row_lane[j]].w |= 1;
+            lane[(size_t)row_dom[i] * TPB + row_lane[i]].w |= 2;
+        }
+    // ring cells of the rows that other domains read, domain by domain in lane order (a
+    // wavefront's stores cover whole cache lines), each domain from a line of its own
+    // where the cells reach
+    int cells = 0;
+    for (int aligned = 1; aligned >= 0; --aligned) {
+        cells = 0;
+        for (int q = 0; q < G; ++q) {
+            if (aligned) cells = (cells + 7) / 8 * 8;
+            for (int t = 0; t < TPB; ++t) {
+                int4& e = lane[(size_t)q * TPB + t];
+                if (e.x >= 0 && e.w) e.z = cells++;
+            }
+        }
+        if (cells <= P.npad) break;
+    }
+    for (const int4& e : lane)
+        if (e.x >= 0 && e.w) {
+            row_cell[e.x] = e.z;
+            cell_row[e.z] = e.x;
+        }
+    std::vector<int> dep_ptr, dep_idx, halo_ptr, halo, ahalo_ptr, ahalo, qlat;
+    domain_deps(h, row_dom, G, dep_ptr, dep_idx);
+    const int hmax = domain_halos(h, row_dom, row_cell, G, false, halo_ptr, halo);
+    const int ahmax = domain_halos(h, row_dom, row_cell, G, true, ahalo_ptr, ahalo);
+    const int halo_cap = tmm::kHaloPerThread * TPB;
+    if (hmax > halo_cap || ahmax > halo_cap || dep_idx.size() > P.dep_capacity || halo.size() > P.halo_capacity ||
+        ahalo.size() > P.halo_capacity)
+        return TMM_OK;
+    // LDS cell of what each entry reads: a lane of the domain, or its place in the halo
+    auto lds_cells = [&](const std::vector<int>& col, int width, const std::vector<int>& ptr, const std::vector<int>& hl) {
+        std::vector<int> out((size_t)tmm::kBinEll * P.npad, 0);
+        for (int s = 0; s < width; ++s)
+            for (int i = 0; i < P.n; ++i) {
+                const int r = col[(size_t)s * P.npad + i], q = row_dom[i];
+                out[(size_t)s * P.npad + i] =
+                    row_dom[r] == q ? row_lane[r]
+                                    : TPB + (int)(std::lower_bound(hl.begin() + ptr[q], hl.begin() + ptr[q + 1], row_cell[r]) -
+                                                  (hl.begin() + ptr[q]));
+            }
+        return out;
+    };
+    const std::vector<int> ae = lds_cells(h->ell_col, P.ew, halo_ptr, halo);
+    const std::vector<int> aet = lds_cells(h->ellt_col, P.etw, ahalo_ptr, ahalo);
+    const int qrows = domain_latitudes(P, lay.cols, qlat);
+    const bool ql = qrows > 0;
+    int dev = 0, lds_max = 0;
+    TMM_TRY(hipGetDevice(&dev));
+    TMM_TRY(hipDeviceGetAttribute(&lds_max, hipDeviceAttributeMaxSharedMemoryPerBlock, dev));
+    h->bins = hb;
+    auto fits = [&](const void* fk, size_t dyn, bool& ok) -> int {
+        hipFuncAttributes attr;
+        TMM_TRY(hipFuncGetAttributes(&attr, fk));
+        ok = attr.sharedSizeBytes + dyn <= (size_t)lds_max;
+        if (!ok) return TMM_OK;
+        TMM_TRY(ensure_dyn_lds(fk, dyn));
+        int o = 0;
+        TMM_TRY(hipOccupancyMaxActiveBlocksPerMultiprocessor(&o, fk, TPB, dyn));
+        ok = o > 0;
+        return TMM_OK;
+    };
+    bool ok = true, adj_ok = false;
+    int rc = TMM_OK;
+    for (int t = 0; t < 2 && rc == TMM_OK && ok; ++t)
+        rc = fits(bins_year_kernel(h, t, ql), tmm::bins_year_lds(hmax, P.ntr, t), ok);
+    if (rc == TMM_OK && ok)
+        rc = fits(bins_adjoint_kernel(h), tmm::bins_adjoint_lds(ahmax, P.ntr, P.nsub > 1 ? P.nsub : 0), adj_ok);
+    if (rc || !ok) {
+        h->bins = 0;
+        return rc;
+    }
+    if (dep_idx.empty()) dep_idx.push_back(0);
+    if (halo.empty()) halo.push_back(0);
+    if (ahalo.empty()) ahalo.push_back(0);
+    const std::vector<int> block_dom = xcd_order(G);
+    if (upload(h, h->at<int>(P.o_pblock), block_dom.data(), (size_t)G * 4) ||
+        upload(h, h->at<int>(P.o_pdepptr), dep_ptr.data(), dep_ptr.size() * 4) ||
+        upload(h, h->at<int>(P.o_pdepidx), dep_idx.data(), dep_idx.size() * 4) ||
+        upload(h, h->at<int>(P.o_phaloptr), halo_ptr.data(), halo_ptr.size() * 4) ||
+        upload(h, h->at<int>(P.o_phalo), halo.data(), halo.size() * 4) ||
+        upload(h, h->at<int>(P.o_pahaloptr), ahalo_ptr.data(), ahalo_ptr.size() * 4) ||
+        upload(h, h->at<int>(P.o_pahalo), ahalo.data(), ahalo.size() * 4) ||
+        upload(h, h->at<int>(P.o_pqlat), qlat.data(), qlat.size() * 4) ||
+        upload(h, h->at<int4>(P.o_blane), lane.data(), lane.size() * 16) ||
+        upload(h, h->at<int>(P.o_bae), ae.data(), ae.size() * 4) ||
+        upload(h, h->at<int>(P.o_baet), aet.data(), aet.size() * 4) ||
+        upload(h, h->at<int>(P.o_bcell), cell_row.data(), cell_row.size() * 4)) {
+        h->bins = 0;
+        return TMM_EDEVICE;
+    }
+    hipLaunchKernelGGL(tmm::k_fill_int, dim3(1), dim3(64), 0, h->stream, h->at<int>(P.o_pabort), 16, 0);
+    TMM_LAUNCHED();
+    TMM_TRY(hipStreamSynchronize(h->stream));
+    h->pers_G = G;
+    h->pers_M = std::max(1, std::min(P.pers_members, ncu / G));
+    h->pers_tpb = TPB;
+    h->pers_hmax = hmax;
+    h->pers_ahmax = ahmax;
+    h->pers_qmax = std::max(qrows, 0);
+    h->pers_ql[0] = h->pers_ql[1] = ql;
+    h->pers_wave_local = true;
+    h->pers_ok = true;
+    h->pers_adj_ok = adj_ok;
+    return TMM_OK;
+}
+
 // Domains for the persistent kernel: contiguous runs of water columns with
 // about n/G rows each (at most the workgroup size), the domains each one must
 // wait for (both directions of every explicit-matrix coupling), and an
@@ -1022,9 +1437,14 @@ int build_persistent(tmm_ctx* h, int target_rows) {
     h->pers_ok = false;
     h->pers_adj_ok = false;
     h->pers_target = target_rows;
+    h->bins = 0;
     if (!coop || !P.o_ring || P.ew > tmm::kEllMax || P.nlayer > 32 || P.neu > tmm::kNeuMax) return TMM_OK;
     h->pers_kmax = P.nlayer <= 16 ? 16 : 32;
     if (target_rows < 1) target_rows = kDefaultDomainRows;
+    if (P.bins_possible && h->wave_local_enabled && target_rows <= tmm::kBinThreads) {
+        const int rc = build_bins(h, target_rows, ncu);
+        if (rc || h->bins) return rc;
+    }
     // 512-thread workgroups only where the row's Ai block fits the halved register budget
     const int tpb = (target_rows > 256 && h->pers_kmax == 16) ? tmm::kPersistThreadsMax : 256;
     target_rows = std::min(target_rows, tpb);
@@ -1109,61 +1529,18 @@ int build_persistent(tmm_ctx* h, int target_rows) {
     std::vector<int> row_dom(P.n);
     for (int q = 0; q < G; ++q)
         for (int r = P.col_start[dom[q]]; r < P.col_start[dom[q + 1]]; ++r) row_dom[r] = q;
-    std::vector<std::vector<int>> deps(G);
-    for (int i = 0; i < P.n; ++i)
-        for (int e = h->ae_rowptr[i]; e < h->ae_rowptr[i + 1]; ++e) {
-            const int a = row_dom[i], b = row_dom[h->ae_colidx[e]];
-            if (a != b) {
-                deps[a].push_back(b);
-                deps[b].push_back(a);
-            }
-        }
-    std::vector<int> dep_ptr(G + 1, 0), dep_idx;
-    for (int q = 0; q < G; ++q) {
-        std::sort(deps[q].begin(), deps[q].end());
-        deps[q].erase(std::unique(deps[q].begin(), deps[q].end()), deps[q].end());
-        dep_idx.insert(dep_idx.end(), deps[q].begin(), deps[q].end());
-        dep_ptr[q + 1] = (int)dep_idx.size();
-    }
+    std::vector<int> dep_ptr, dep_idx;
+    domain_deps(h, row_dom, G, dep_ptr, dep_idx);
     if (dep_idx.size() > P.dep_capacity) return TMM_OK;
     if (dep_idx.empty()) dep_idx.push_back(0);
-    // halo of each domain: the rows of other domains its Ae rows read, ascending
-    std::vector<int> halo_ptr(G + 1, 0), halo;
-    int hmax = 0;
-    for (int q = 0; q < G; ++q) {
-        std::vector<int> hq;
-        for (int i = P.col_start[dom[q]]; i < P.col_start[dom[q + 1]]; ++i)
-            for (int e = h->ae_rowptr[i]; e < h->ae_rowptr[i + 1]; ++e)
-                if (row_dom[h->ae_colidx[e]] != q) hq.push_back(h->ae_colidx[e]);
-        std::sort(hq.begin(), hq.end());
-        hq.erase(std::unique(hq.begin(), hq.end()), hq.end());
-        if (hq.size() > halo_cap) return TMM_OK;          // does not fit: per-step path only
-        hmax = std::max(hmax, (int)hq.size());
-        halo.insert(halo.end(), hq.begin(), hq.end());
-        halo_ptr[q + 1] = (int)halo.size();
-    }
-    if (halo.size() > P.halo_capacity) return TMM_OK;
+    // halos, for Ae and (the reverse sweep) its transpose
+    std::vector<int> rows(P.n), halo_ptr, halo, ahalo_ptr, ahalo;
+    for (int i = 0; i < P.n; ++i) rows[i] = i;
+    const int hmax = domain_halos(h, row_dom, rows, G, false, halo_ptr, halo);
+    if (hmax > (int)halo_cap || halo.size() > P.halo_capacity) return TMM_OK;   // does not fit: per-step path only
     if (halo.empty()) halo.push_back(0);
-    // halo of the transposed stencil: row i of Ae^T reads mu at the rows whose
-    // Ae rows have an entry in column i
-    std::vector<std::vector<int>> ah(G);
-    for (int i = 0; i < P.n; ++i)
-        for (int e = h->ae_rowptr[i]; e < h->ae_rowptr[i + 1]; ++e) {
-            const int q = row_dom[h->ae_colidx[e]];
-            if (row_dom[i] != q) ah[q].push_back(i);
-        }
-    std::vector<int> ahalo_ptr(G + 1, 0), ahalo;
-    int ahmax = 0;
-    bool ahalo_ok = true;
-    for (int q = 0; q < G; ++q) {
-        std::sort(ah[q].begin(), ah[q].end());
-        ah[q].erase(std::unique(ah[q].begin(), ah[q].end()), ah[q].end());
-        if (ah[q].size() > halo_cap) ahalo_ok = false;
-        ahmax = std::max(ahmax, (int)ah[q].size());
-        ahalo.insert(ahalo.end(), ah[q].begin(), ah[q].end());
-        ahalo_ptr[q + 1] = (int)ahalo.size();
-    }
-    if (ahalo.size() > P.halo_capacity) ahalo_ok = false;
+    int ahmax = domain_halos(h, row_dom, rows, G, true, ahalo_ptr, ahalo);
+    const bool ahalo_ok = ahmax <= (int)halo_cap && ahalo.size() <= P.halo_capacity;
     if (!ahalo_ok) {                                      // the reverse sweep falls back to per-step kernels
         ahmax = 0;
         ahalo.assign(1, 0);
@@ -1173,21 +1550,13 @@ int build_persistent(tmm_ctx* h, int target_rows) {
     // latitude rows of each domain's columns: without internal BGC steps the
     // forward kernels keep the insolation of those rows for the whole year in
     // LDS beside their halo, where it fits (else they load it every step)
-    std::vector<int> qlat((size_t)G * (1 + tmm::kInsLat), 0);
-    int qmax = 0;
-    bool ql = sn == 0;
-    for (int q = 0; q < G && ql; ++q) {
-        int* e = qlat.data() + (size_t)q * (1 + tmm::kInsLat);
-        for (int c = dom[q]; c < dom[q + 1] && ql; ++c) {
-            const int l = P.col_lat[c];
-            bool seen = false;
-            for (int i = 0; i < e[0]; ++i) seen = seen || e[1 + i] == l;
-            if (seen) continue;
-            if (e[0] == tmm::kInsLat) ql = false;
-            else e[1 + e[0]++] = l;
-        }
-        qmax = std::max(qmax, e[0]);
-    }
+    std::vector<std::vector<int>> dom_cols(G);
+    for (int q = 0; q < G; ++q)
+        for (int c = dom[q]; c < dom[q + 1]; ++c) dom_cols[q].push_back(c);
+    std::vector<int> qlat;
+    int qmax = domain_latitudes(P, dom_cols, qlat);
+    const bool ql = sn == 0 && qmax > 0;
+    qmax = std::max(qmax, 0);
     // decided per mode: the tangent's larger LDS may not leave room for the
     // table (or for the co-residency of all domains) where the state's does
     bool ql_mode[2] = {ql, ql};
@@ -1203,15 +1572,10 @@ int build_persistent(tmm_ctx* h, int target_rows) {
         TMM_TRY(ensure_dyn_lds(fk, dyn));
         int o = 0;
         TMM_TRY(hipOccupancyMaxActiveBlocksPerMultiprocessor(&o, fk, tpb, dyn));
-        if ((long long)ncu * o < G) ql_mode[t] = false;
+        if ((long long)ncu * o < (long long)std::max(1, std::min(P.pers_members, maxG / G)) * G) ql_mode[t] = false;
     }
     if (!ql_mode[0] && !ql_mode[1]) qmax = 0;
-    std::vector<int> block_dom(G);
-    {
-        int next = 0;
-        for (int x = 0; x < 8; ++x)
-            for (int b = x; b < G; b += 8) block_dom[b] = next++;
-    }
+    const std::vector<int> block_dom = xcd_order(G);
     if (upload(h, h->at<int>(P.o_pblock), block_dom.data(), (size_t)G * 4) ||
         upload(h, h->at<int>(P.o_pdomcol), dom.data(), dom.size() * 4) ||
         upload(h, h->at<int>(P.o_pdepptr), dep_ptr.data(), dep_ptr.size() * 4) ||
@@ -1227,6 +1591,7 @@ int build_persistent(tmm_ctx* h, int target_rows) {
     TMM_LAUNCHED();
     TMM_TRY(hipStreamSynchronize(h->stream));
     h->pers_G = G;
+    h->pers_M = std::max(1, std::min(P.pers_members, maxG / G));
     h->pers_tpb = tpb;
     h->pers_hmax = hmax;
     h->pers_ahmax = ahmax;
@@ -1235,7 +1600,7 @@ int build_persistent(tmm_ctx* h, int target_rows) {
     h->pers_ql[1] = ql_mode[1];
     h->pers_wave_local = wave_local;
     h->pers_ok = true;
-    h->pers_adj_ok = ahalo_ok && (long long)ncu * occ_adj >= G;
+    h->pers_adj_ok = ahalo_ok && (long long)ncu * occ_adj >= (long long)h->pers_M * G;
     return TMM_OK;
 }
 
@@ -1259,20 +1624,23 @@ int sqdiff(tmm_ctx* h, int nb, const double* a, const double* b, int volume, dou
 
 
 
-// Checkpointed adjoint of one model year for one member with persistent
-// launches: a forward sweep storing y every ckpt steps and the month-end
-// misfit sums; the misfit source of the last month and Ai^T for the last
-// step; then per segment, last first, a forward replay storing every state
-// and a reverse sweep over the segment.  The forward sweep writes the last
-// segment's states straight into the segment store, so that segment is not
-// replayed; with one segment (ckpt = nstep) nothing is.
-int adjoint_persistent(tmm_ctx* h, const double* y0, const double* obs, double* J_host, double* dJdu_host,
+// Checkpointed adjoint of one model year with persistent launches, for nb
+// members, pers_M at a time: a forward sweep storing y every ckpt steps and
+// the month-end misfit sums; the misfit source of the last month and Ai^T for
+// the last step; then per segment, last first, a forward replay storing every
+// state and a reverse sweep over the segment.  The forward sweep writes the
+// last segment's states straight into the segment store, so that segment is
+// not replayed; with one segment (ckpt = nstep) nothing is.  Checkpoints and
+// segment stores are kept member after member.
+int adjoint_persistent(tmm_ctx* h, int nb, const double* y0, const double* obs, double* J_host, double* dJdu_host,
                        double* dJdy0) {
     const Plan& P = h->P;
-    const int np = P.nparam, G = h->pers_G;
-    const size_t len = (size_t)P.n * P.ntr;
+    const int np = P.nparam, G = h->pers_G, W = nb * P.ntr;
+    const size_t slen = (size_t)P.n * P.ntr, len = (size_t)P.n * W;
     const int K = P.ckpt, nseg = P.nstep / K;
+    const size_t ckpt_step = (size_t)nseg * slen, seg_step = (size_t)K * slen;
     const double dtd = tmm::kDaysPerYear / P.nstep;
+    const double scale = 1.0 / (P.nmat * h->vtot);
     double* ckpt = h->at<double>(P.o_ckpt);
     double* seg = h->at<double>(P.o_seg);
     double* fin = h->at<double>(P.o_final);
@@ -1280,76 +1648,87 @@ int adjoint_persistent(tmm_ctx* h, const double* y0, const double* obs, double* 
     double* ubar = h->at<double>(P.o_pubar);
     double* jpart = h->at<double>(P.o_pjpart);
     int rc;
-    if ((rc = fill(h, ubar, (size_t)G * np, 0.0)) || (rc = fill(h, jpart, (size_t)P.nmat * G, 0.0))) return rc;
+    if ((rc = fill(h, ubar, (size_t)G * nb * np, 0.0)) || (rc = fill(h, jpart, (size_t)P.nmat * G * nb, 0.0))) return rc;
     // forward sweep: checkpoints y_{sK} at slot s up to the last segment, whose
     // states y_lo .. y_{nstep-1} go to the segment store; misfit partial sums
     const int lo_last = (nseg - 1) * K;
-    const double* ylast = y0;
-    if (nseg > 1) {
-        tmm::StepRange fw{0, lo_last, ckpt, K, obs, jpart};
-        double* yl = ckpt + (size_t)(nseg - 1) * len;
-        if ((rc = launch_persistent(h, fw, y0, yl)))
-            return rc;
-        ylast = yl;
+    for (int s = 0; s < nb; s += h->pers_M) {
+        const int M = std::min(h->pers_M, nb - s);
+        const tmm::StateView ob = batch_view(h, obs, W, s);
+        double* ck = ckpt + (size_t)s * ckpt_step;
+        tmm::StateView from = batch_view(h, y0, W, s);
+        if (nseg > 1) {
+            tmm::StepRange fw{0, lo_last, ck, K, ckpt_step, ob, len, jpart + s, nb};
+            const tmm::StateView yl = compact_view(h, ck + (size_t)(nseg - 1) * slen, ckpt_step);
+            if ((rc = launch_persistent(h, M, s, fw, from, yl))) return rc;
+            from = yl;
+        }
+        tmm::StepRange fl{lo_last, P.nstep, seg + (size_t)s * seg_step, 1, seg_step, ob, len, jpart + s, nb};
+        if ((rc = launch_persistent(h, M, s, fl, from, batch_view(h, fin, W, s)))) return rc;
     }
-    {
-        tmm::StepRange fl{lo_last, P.nstep, seg, 1, obs, jpart};
-        if ((rc = launch_persistent(h, fl, ylast, fin)))
-            return rc;
-    }
-    hipLaunchKernelGGL(tmm::k_sum_tiles, dim3(1), dim3(64), 0, h->stream, P.nmat * G, 1, 1, jpart,
-                       1.0 / (2.0 * P.nmat * h->vtot), 0, 0, h->vec(4));
+    hipLaunchKernelGGL(tmm::k_sum_tiles, dim3(1), dim3(256), 0, h->stream, P.nmat * G, nb, nb, jpart, 0.5 * scale, 0, 0,
+                       h->vec(4));
     TMM_LAUNCHED();
     // head: lambda_nstep = source of the last month, mu_{nstep-1} = Ai(t_{nstep-1})^T lambda_nstep
     {
-        const Tiling& tl = h->tiling_for(P.ntr, 1, 256 * 8 * np);
+        const Tiling& tl = h->tiling_for(W, 1, 256 * 8 * np);
         tmm::Grid g = h->grid(tl);
         tmm::Model md = h->model();
         tmm::Mats mt = h->mats();
-        const size_t lds = (size_t)tl.max_rows * P.ntr * 8 + (size_t)256 * np * 8;
-        const double sc = 1.0 / (P.nmat * h->vtot);
+        const size_t lds = (size_t)tl.max_rows * W * 8 + (size_t)256 * np * 8;
         const double* ob = obs + (size_t)(P.nmat - 1) * len;
         if (P.ntr == 3)
             hipLaunchKernelGGL((tmm::k_adjoint<3, kMaxTileRows, kMaxTileRows>), dim3(tl.ntile), dim3(256), lds,
-                               h->stream, g, md, mt, P.ntr, 1, P.nstep, dtd, 0, 1, nullptr, fin, ob, sc, mu[0],
+                               h->stream, g, md, mt, W, nb, P.nstep, dtd, 0, 1, nullptr, fin, ob, scale, mu[0],
                                nullptr);
         else if (P.ntr == 2)
             hipLaunchKernelGGL((tmm::k_adjoint<2, kMaxTileRows, kMaxTileRows>), dim3(tl.ntile), dim3(256), lds,
-                               h->stream, g, md, mt, P.ntr, 1, P.nstep, dtd, 0, 1, nullptr, fin, ob, sc, mu[0],
+                               h->stream, g, md, mt, W, nb, P.nstep, dtd, 0, 1, nullptr, fin, ob, scale, mu[0],
                                nullptr);
         else
             hipLaunchKernelGGL((tmm::k_adjoint<1, kMaxTileRows, kMaxTileRows>), dim3(tl.ntile), dim3(256), lds,
-                               h->stream, g, md, mt, P.ntr, 1, P.nstep, dtd, 0, 1, nullptr, fin, ob, sc, mu[0],
+                               h->stream, g, md, mt, W, nb, P.nstep, dtd, 0, 1, nullptr, fin, ob, scale, mu[0],
                                nullptr);
         TMM_LAUNCHED();
     }
-    int im = 0;
-    for (int sg = nseg - 1; sg >= 0; --sg) {
-        const int lo = sg * K, hi = lo + K;
-        // replay: y_lo .. y_{hi-1} into the segment store (the forward sweep
-        // left the last segment there)
-        tmm::StepRange rp{lo, hi, seg, 1, nullptr, nullptr};
-        if (sg < nseg - 1 &&
-            (rc = launch_persistent(h, rp, ckpt + (size_t)sg * len, h->ybuf(2))))
-            return rc;
-        double* out = sg == 0 ? (dJdy0 ? dJdy0 : mu[1 - im]) : mu[1 - im];
-        if ((rc = launch_adjoint_persistent(h, lo, hi, seg, obs, 1.0 / (P.nmat * h->vtot), mu[im], out, ubar)))
-            return rc;
-        im = 1 - im;
+    for (int s = 0; s < nb; s += h->pers_M) {
+        const int M = std::min(h->pers_M, nb - s);
+        const tmm::StateView ob = batch_view(h, obs, W, s);
+        double* sg_store = seg + (size_t)s * seg_step;
+        int im = 0;
+        for (int sg = nseg - 1; sg >= 0; --sg) {
+            const int lo = sg * K, hi = lo + K;
+            // replay: y_lo .. y_{hi-1} into the segment store (the forward sweep
+            // left the last segment there)
+            tmm::StepRange rp{lo, hi, sg_store, 1, seg_step, {}, 0, nullptr, 1};
+            if (sg < nseg - 1 &&
+                (rc = launch_persistent(h, M, s, rp,
+                                        compact_view(h, ckpt + (size_t)s * ckpt_step + (size_t)sg * slen, ckpt_step),
+                                        batch_view(h, h->ybuf(2), W, s))))
+                return rc;
+            double* out = sg == 0 ? (dJdy0 ? dJdy0 : mu[1 - im]) : mu[1 - im];
+            if ((rc = launch_adjoint_persistent(h, M, s, lo, hi, sg_store, seg_step, ob, len, scale,
+                                                batch_view(h, mu[im], W, s), batch_view(h, out, W, s),
+                                                ubar + (size_t)s * np, nb)))
+                return rc;
+            im = 1 - im;
+        }
     }
-    hipLaunchKernelGGL(tmm::k_sum_tiles, dim3(1), dim3(64), 0, h->stream, G, np, np, ubar, 1.0, 0, 0, h->vec(5));
+    hipLaunchKernelGGL(tmm::k_sum_tiles, dim3(1), dim3(256), 0, h->stream, G, nb * np, nb * np, ubar, 1.0, 0, 0,
+                       h->vec(5));
     TMM_LAUNCHED();
-    double J = 0.0;
-    std::vector<double> Gr(np);
-    TMM_TRY(hipMemcpyAsync(&J, h->vec(4), 8, hipMemcpyDeviceToHost, h->stream));
-    TMM_TRY(hipMemcpyAsync(Gr.data(), h->vec(5), (size_t)np * 8, hipMemcpyDeviceToHost, h->stream));
+    std::vector<double> J(nb), Gr((size_t)nb * np);
+    TMM_TRY(hipMemcpyAsync(J.data(), h->vec(4), (size_t)nb * 8, hipMemcpyDeviceToHost, h->stream));
+    TMM_TRY(hipMemcpyAsync(Gr.data(), h->vec(5), (size_t)nb * np * 8, hipMemcpyDeviceToHost, h->stream));
     TMM_TRY(hipStreamSynchronize(h->stream));
     if ((rc = check_abort(h))) return rc;
-    if (!std::isfinite(J)) return TMM_ENONFINITE;
-    J_host[0] = J;
-    for (int q = 0; q < np; ++q) {
-        if (!std::isfinite(Gr[q])) return TMM_ENONFINITE;
-        dJdu_host[q] = Gr[q];
+    for (int b = 0; b < nb; ++b) {
+        if (!std::isfinite(J[b])) return TMM_ENONFINITE;
+        J_host[b] = J[b];
+    }
+    for (size_t i = 0; i < Gr.size(); ++i) {
+        if (!std::isfinite(Gr[i])) return TMM_ENONFINITE;
+        dJdu_host[i] = Gr[i];
     }
     return TMM_OK;
 }
@@ -1446,6 +1825,7 @@ int tmm_create(const tmm_desc* d, void* dev_workspace, size_t bytes, void* hip_s
         for (int c = 0; c < P.npad; ++c)
             for (int s = tlen[c]; s < P.etw; ++s) tcol[(size_t)s * P.npad + c] = c < P.n ? c : 0;
         if (upload(h, h->at<int>(P.o_aetcol), tcol.data(), tcol.size() * 4)) return fail(TMM_EDEVICE);
+        h->ellt_col = tcol;
         std::vector<double> tval((size_t)P.etw * P.npad);
         for (int m = 0; m < P.nmat; ++m) {
             std::fill(tval.begin(), tval.end(), 0.0);
@@ -1993,8 +2373,8 @@ int tmm_year_adjoint(tmm_handle h, const double* y0, const double* obs, int ckpt
     const size_t n = P.n, len = n * W;
     const int K = P.ckpt, spm = P.nstep / P.nmat, nseg = P.nstep / K;
     const double dtd = tmm::kDaysPerYear / P.nstep;
-    if (nb == 1 && h->pers_ok && h->pers_adj_ok && h->pers_enabled && P.etw <= tmm::kEllMax)
-        return adjoint_persistent(h, y0, obs, J_host, dJdu_host, dJdy0);
+    if (h->pers_adj_ok && P.etw <= tmm::kEllMax && single_launch(h, nb, true))
+        return adjoint_persistent(h, nb, y0, obs, J_host, dJdu_host, dJdy0);
     const Tiling& tl = h->tiling_for(W, 1, 256 * 8 * np);
     tmm::Grid g = h->grid(tl);
     tmm::Model md = h->model();

@@ -83,6 +83,26 @@ __device__ __forceinline__ BgcParams load_params(const double* __restrict__ u, i
     return load_params_at(u, model, (size_t)nparam, 1, m);
 }
 
+// The roundings of a two-tracer step without internal BGC steps are written
+// out (fused multiply-adds by name, nothing left to the compiler to contract),
+// so that the member-parallel, the single-launch and their packed variants
+// give the same bits whatever else their loops hold.
+__device__ __forceinline__ double lerp(double a0, double a1, double w) {
+#pragma clang fp contract(off)
+    return __builtin_fma(w, a1 - a0, a0);
+}
+
+// Sources of one row of the N / PO4-DOP models: q1 = -f + lambda DOP +
+// (1 - sigma) Phi rho, q2 = sigma f - lambda DOP (section 2.2.1).
+__device__ __forceinline__ void row_q(const BgcParams& p, double f, double dop, double Phi, double rho, double& q1,
+                                      double& q2) {
+#pragma clang fp contract(off)
+    const double ld = p.lam * dop;
+    const double e = (1.0 - p.sig) * Phi;
+    q1 = __builtin_fma(e, rho, ld - f);
+    q2 = __builtin_fma(p.sig, f, -ld);
+}
+
 // Month pair and weight of step j: monthly matrices sit at mid-month and the
 // year is periodic (section 3).  Integer arithmetic, one exact division.
 __device__ __forceinline__ void step_phase(int j, int nstep, int nmat, int& k0, int& k1, double& w) {
@@ -115,7 +135,7 @@ __device__ __forceinline__ double insolation(double lat_deg, double t) {
 
 // Insolation table ins[j][l] = I_SWR(lat_l, j/nstep) for every step of the year
 // and every distinct latitude of the grid (computed once per handle).
-__global__ void k_insolation_table(int nstep, int nlat, const double* __restrict__ lat_u,
+[[maybe_unused]] static __global__ void k_insolation_table(int nstep, int nlat, const double* __restrict__ lat_u,
                                    double* __restrict__ ins) {
     const int idx = blockIdx.x * blockDim.x + threadIdx.x;
     if (idx >= nstep * nlat) return;
@@ -149,7 +169,7 @@ __device__ __forceinline__ Production production(const BgcParams& p, double N, d
 // member-fastest copies lightT[k][m] and rhoT[n_c*nlayer + k][m] (member
 // stride nbm) serve the member-parallel kernel, whose lanes are members.
 // ---------------------------------------------------------------------------
-__global__ void k_param_tables(int nbatch, int model, int nparam, int nlayer, int neu,
+[[maybe_unused]] static __global__ void k_param_tables(int nbatch, int model, int nparam, int nlayer, int neu,
                                const double* __restrict__ u, const double* __restrict__ dz,
                                double* __restrict__ light, double* __restrict__ rho,
                                double* __restrict__ drho, int nbm, double* __restrict__ lightT,
@@ -779,7 +799,6 @@ __global__ __launch_bounds__(64 * WAVES) void k_step_members(Grid g, Model md, M
     int k0, k1;
     double w;
     step_phase(j, g.nstep, g.nmat, k0, k1, w);
-    const double om = 1.0 - w;
 
     // the member's parameters and light factors, the column's insolation and
     // euphotic state: loaded before the staging below so that their latency
@@ -814,7 +833,7 @@ __global__ __launch_bounds__(64 * WAVES) void k_step_members(Grid g, Model md, M
             const int k = i / KMAX, sl = i % KMAX;
             const bool in = i < KMAX * KMAX && k < nc && sl < nc;
             const int at = in ? k * nc + sl : 0;
-            const double v = om * ai0[at] + w * ai1[at];
+            const double v = lerp(ai0[at], ai1[at], w);
             if (i < KMAX * KMAX) s_ai[cs][i] = in ? v : 0.0;
         }
         const double* ae0 = mt.ae + (size_t)k0 * mt.ae_month;
@@ -827,7 +846,7 @@ __global__ __launch_bounds__(64 * WAVES) void k_step_members(Grid g, Model md, M
             const bool in = i < KMAX * EL && k < nc && sl < mt.ew;
             const size_t e = in ? (size_t)sl * g.npad + rs + k : (size_t)rs;
             const int col = mt.ae_col[e];
-            const double v = om * ae0[e] + w * ae1[e];
+            const double v = lerp(ae0[e], ae1[e], w);
             if (i < KMAX * EL) {
                 s_off[cs][i] = (uint32_t)(in ? col : rs) * (uint32_t)(W * 8);
                 s_ae[cs][i] = in ? v : 0.0;
@@ -843,7 +862,7 @@ __global__ __launch_bounds__(64 * WAVES) void k_step_members(Grid g, Model md, M
         f[e] = 0.0;
         if (e < ne) {
             f[e] = production(p, Ne[e], Q, le[e]).f;
-            Phi += g.dz[e] * f[e];
+            Phi = __builtin_fma(g.dz[e], f[e], Phi);
         }
     }
 
@@ -906,7 +925,7 @@ __global__ __launch_bounds__(64 * WAVES) void k_step_members(Grid g, Model md, M
         for (int sl = 0; sl < EL; ++sl) {
             const double a = s_ae[cs][k * EL + sl];
 #pragma unroll
-            for (int t = 0; t < NTR; ++t) acc[t] += a * yv[sl][t];
+            for (int t = 0; t < NTR; ++t) acc[t] = __builtin_fma(a, yv[sl][t], acc[t]);
         }
         if (SUB) {
             double src[NTR];
@@ -925,9 +944,10 @@ __global__ __launch_bounds__(64 * WAVES) void k_step_members(Grid g, Model md, M
 #pragma unroll
             for (int e = 0; e < NEU; ++e)
                 if (e == k) fk = f[e];
-            const double q1 = -fk + p.lam * dop + (1.0 - p.sig) * Phi * rho;
-            z[k][0] = acc[0] + dtd * q1;
-            if (NTR > 1) z[k][NTR - 1] = acc[NTR - 1] + dtd * (p.sig * fk - p.lam * dop);
+            double q1, q2;
+            row_q(p, fk, dop, Phi, rho, q1, q2);
+            z[k][0] = __builtin_fma(dtd, q1, acc[0]);
+            if (NTR > 1) z[k][NTR - 1] = __builtin_fma(dtd, q2, acc[NTR - 1]);
         }
     }
 
@@ -940,7 +960,7 @@ __global__ __launch_bounds__(64 * WAVES) void k_step_members(Grid g, Model md, M
         for (int sl = 0; sl < KMAX; ++sl) {
             const double a = s_ai[cs][k * KMAX + sl];
 #pragma unroll
-            for (int t = 0; t < NTR; ++t) acc[t] += a * z[sl][t];
+            for (int t = 0; t < NTR; ++t) acc[t] = __builtin_fma(a, z[sl][t], acc[t]);
         }
         if (act) {
             double* dst = yo + (size_t)(rs + k) * W + me;
@@ -1014,7 +1034,6 @@ __global__ __launch_bounds__(64 * T) void k_step_member_tiles(Grid g, Model md, 
     int k0, k1;
     double w;
     step_phase(j, g.nstep, g.nmat, k0, k1, w);
-    const double om = 1.0 - w;
     const int m = md.member[bb];
     const double* rhoc = md.rhoT + (size_t)nc * g.nlayer * md.nbm + m;   // rho_k of this depth at [k * nbm]
 
@@ -1073,7 +1092,7 @@ __global__ __launch_bounds__(64 * T) void k_step_member_tiles(Grid g, Model md, 
             const int k = i / KMAX, sl = i % KMAX;
             const bool in = i < KMAX * KMAX && k < nc && sl < nc;
             const int at = in ? k * nc + sl : 0;
-            const double v = om * ai0[at] + w * ai1[at];
+            const double v = lerp(ai0[at], ai1[at], w);
             if (i < KMAX * KMAX) s_ai[wave][i] = in ? v : 0.0;
         }
         const double* ae0 = mt.ae + (size_t)k0 * mt.ae_month;
@@ -1086,7 +1105,7 @@ __global__ __launch_bounds__(64 * T) void k_step_member_tiles(Grid g, Model md, 
             const int k = i / EL, sl = i % EL;
             const bool in = i < KMAX * EL && k < nc && sl < mt.ew;
             const size_t e = in ? (size_t)sl * g.npad + rs + k : (size_t)rs;
-            const double v = om * ae0[e] + w * ae1[e];
+            const double v = lerp(ae0[e], ae1[e], w);
             const int ii = i < KMAX * EL ? i : 0;
             const uint32_t at = (uint32_t)li[ii] * (uint32_t)(64 * sizeof(double2));
             if (i < KMAX * EL) {
@@ -1102,7 +1121,7 @@ __global__ __launch_bounds__(64 * T) void k_step_member_tiles(Grid g, Model md, 
         f[e] = 0.0;
         if (e < ne) {
             f[e] = production(p, Ne[e], Q, le[e]).f;
-            Phi += g.dz[e] * f[e];
+            Phi = __builtin_fma(g.dz[e], f[e], Phi);
         }
     }
 
@@ -1134,15 +1153,16 @@ __global__ __launch_bounds__(64 * T) void k_step_member_tiles(Grid g, Model md, 
         for (int sl = 0; sl < EL; ++sl) {
             const double a = s_ae[wave][k * EL + sl];
 #pragma unroll
-            for (int t = 0; t < NTR; ++t) acc[t] += a * yv[sl][t];
+            for (int t = 0; t < NTR; ++t) acc[t] = __builtin_fma(a, yv[sl][t], acc[t]);
         }
         double fk = 0.0;
 #pragma unroll
         for (int e = 0; e < NEU; ++e)
             if (e == k) fk = f[e];
-        const double q1 = -fk + p.lam * dop + (1.0 - p.sig) * Phi * rho;
-        z[k][0] = acc[0] + dtd * q1;
-        z[k][1] = acc[1] + dtd * (p.sig * fk - p.lam * dop);
+        double q1, q2;
+        row_q(p, fk, dop, Phi, rho, q1, q2);
+        z[k][0] = __builtin_fma(dtd, q1, acc[0]);
+        z[k][1] = __builtin_fma(dtd, q2, acc[1]);
         // form z here: left alone, the compiler sinks this arithmetic past the
         // remaining layers into the product below and keeps every layer's
         // staged values live instead (spills)
@@ -1156,7 +1176,7 @@ __global__ __launch_bounds__(64 * T) void k_step_member_tiles(Grid g, Model md, 
         for (int sl = 0; sl < KMAX; ++sl) {
             const double a = s_ai[wave][k * KMAX + sl];
 #pragma unroll
-            for (int t = 0; t < NTR; ++t) acc[t] += a * z[sl][t];
+            for (int t = 0; t < NTR; ++t) acc[t] = __builtin_fma(a, z[sl][t], acc[t]);
         }
         if (act) *reinterpret_cast<double2*>(yo + (size_t)(rs + k) * W + me) = make_double2(acc[0], acc[1]);
     }
@@ -1406,7 +1426,7 @@ __global__ void k_tile_volume(Grid g, double* __restrict__ part) {
 }
 
 // out[q] = scale * sum_t part[t*stride + q] (+ out[q] if accumulate); optional sqrt.
-__global__ void k_sum_tiles(int ntile, int stride, int nq, const double* __restrict__ part, double scale,
+[[maybe_unused]] static __global__ void k_sum_tiles(int ntile, int stride, int nq, const double* __restrict__ part, double scale,
                             int accumulate, int take_sqrt, double* __restrict__ out) {
     const int q = blockIdx.x * blockDim.x + threadIdx.x;
     if (q >= nq) return;
@@ -1417,20 +1437,20 @@ __global__ void k_sum_tiles(int ntile, int stride, int nq, const double* __restr
     out[q] = accumulate ? out[q] + s : s;
 }
 
-__global__ void k_fill(double* __restrict__ x, size_t len, double value) {
+[[maybe_unused]] static __global__ void k_fill(double* __restrict__ x, size_t len, double value) {
     size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
     const size_t stride = (size_t)gridDim.x * blockDim.x;
     for (; i < len; i += stride) x[i] = value;
 }
 
-__global__ void k_copy(double* __restrict__ dst, const double* __restrict__ src, size_t len) {
+[[maybe_unused]] static __global__ void k_copy(double* __restrict__ dst, const double* __restrict__ src, size_t len) {
     size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
     const size_t stride = (size_t)gridDim.x * blockDim.x;
     for (; i < len; i += stride) dst[i] = src[i];
 }
 
 // flag = 1 if any of x[0 .. len) is not finite (left alone otherwise).
-__global__ void k_check_finite(const double* __restrict__ x, size_t len, int* __restrict__ flag) {
+[[maybe_unused]] static __global__ void k_check_finite(const double* __restrict__ x, size_t len, int* __restrict__ flag) {
     size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
     const size_t stride = (size_t)gridDim.x * blockDim.x;
     bool bad = false;
@@ -1439,7 +1459,7 @@ __global__ void k_check_finite(const double* __restrict__ x, size_t len, int* __
 }
 
 // FD direction: h_s = 1e-8 ||y_s|| / ||v_s|| per slot from squared norms.
-__global__ void k_fd_step(int nb, const double* __restrict__ ny2, const double* __restrict__ nv2,
+[[maybe_unused]] static __global__ void k_fd_step(int nb, const double* __restrict__ ny2, const double* __restrict__ nv2,
                           double* __restrict__ h) {
     const int s = blockIdx.x * blockDim.x + threadIdx.x;
     if (s >= nb) return;
@@ -1447,7 +1467,7 @@ __global__ void k_fd_step(int nb, const double* __restrict__ ny2, const double* 
 }
 
 // out = y + h_slot v
-__global__ void k_axpy_slots(size_t n, int W, int ntr, const double* __restrict__ h, const double* __restrict__ y,
+[[maybe_unused]] static __global__ void k_axpy_slots(size_t n, int W, int ntr, const double* __restrict__ h, const double* __restrict__ y,
                              const double* __restrict__ v, double* __restrict__ out) {
     size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
     const size_t stride = (size_t)gridDim.x * blockDim.x;
@@ -1455,7 +1475,7 @@ __global__ void k_axpy_slots(size_t n, int W, int ntr, const double* __restrict_
 }
 
 // jv = (fp - f0)/h_slot  (0 where h = 0)
-__global__ void k_fd_quot(size_t n, int W, int ntr, const double* __restrict__ h, const double* __restrict__ fp,
+[[maybe_unused]] static __global__ void k_fd_quot(size_t n, int W, int ntr, const double* __restrict__ h, const double* __restrict__ fp,
                           const double* __restrict__ f0, double* __restrict__ jv) {
     size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
     const size_t stride = (size_t)gridDim.x * blockDim.x;
@@ -1467,7 +1487,7 @@ __global__ void k_fd_quot(size_t n, int W, int ntr, const double* __restrict__ h
 
 // Column gather between state layouts: dst[i*Wd + dcol[s]*ntr + tr] = src[i*Ws + scol[s]*ntr + tr]
 // for s < ns (member compaction and scatter of finished members).
-__global__ void k_gather_slots(size_t n, int ns, int ntr, int Ws, int Wd, const int* __restrict__ scol,
+[[maybe_unused]] static __global__ void k_gather_slots(size_t n, int ns, int ntr, int Ws, int Wd, const int* __restrict__ scol,
                                const int* __restrict__ dcol, const double* __restrict__ src,
                                double* __restrict__ dst) {
     size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;

@@ -97,7 +97,18 @@ struct Persist {
     const int* col_slot;    // [ncol] thread of the forward kernels that holds the first row of
                             // each water column, within its domain's workgroup
     int wave_local;         // 1: no water column spans two wavefronts (see k_year_persistent)
+    size_t ring_len;        // doubles of one member's ring (and vring)
 };
+
+// A state of the launch's members: element (row, tracer) of member ms at
+// p[ms * step + row * ld + t].  Covers the row-major batch (ld = W, step =
+// tracers) and one member's array after another (ld = tracers).
+struct StateView {
+    double* p;
+    int ld;
+    size_t step;
+};
+__device__ __forceinline__ double* member_of(const StateView& v, int ms) { return v.p + (size_t)ms * v.step; }
 
 // Distinct latitude rows a domain may span for its insolation table in LDS.
 constexpr int kInsLat = 8;
@@ -124,10 +135,13 @@ __device__ __forceinline__ void wave_lds_sync() {
 // and month-end misfit partial sums against obs.
 struct StepRange {
     int j0, j1;
-    double* store;          // nullable, [slots][n*NTR]
+    double* store;          // nullable, [slots][n*NTR], member ms at ms * store_step
     int store_every;
-    const double* obs;      // nullable, [nmat][n*NTR]
-    double* jpart;          // [nmat][G] per-domain sums of V_i (y - obs)^2
+    size_t store_step;
+    StateView obs;          // nullable p; month m at m * obs_month
+    size_t obs_month;
+    double* jpart;          // [nmat][G][jpart_ld] per-domain sums of V_i (y - obs)^2, member ms at [ms]
+    int jpart_ld;
 };
 
 // A slot holds one state tracer by tracer ([NTR][n]): the threads of a
@@ -141,14 +155,16 @@ __device__ __forceinline__ size_t ring_at(size_t slot_base, int n, int row, int 
 // form, so that no value equals the sentinel), slots 1 .. K-1 the sentinel.
 // Slots K .. 2K-1 are reset by the kernel itself (step t - K resets the slot
 // of state t) before any read, so whatever they hold from earlier launches
-// is never read.  y is row-major n x ntr.
-__global__ void k_ring_init(double* __restrict__ ring, const double* __restrict__ y, int n, int ntr, size_t total) {
+// is never read.  blockIdx.y = member of the launch.
+[[maybe_unused]] static __global__ void k_ring_init(double* __restrict__ rings, size_t ring_len, StateView yv, int n, int ntr, size_t total) {
     const double sent = __longlong_as_double(kSentinelBits);
     const size_t slen = (size_t)n * ntr;
+    double* const ring = rings + (size_t)blockIdx.y * ring_len;
+    const double* const y = member_of(yv, blockIdx.y);
     for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < total; i += (size_t)gridDim.x * blockDim.x) {
         if (i < slen) {
             const int t = (int)(i / n), row = (int)(i % n);
-            ring[i] = publishable(y[(size_t)row * ntr + t]);
+            ring[i] = publishable(y[(size_t)row * yv.ld + t]);
         } else {
             ring[i] = sent;
         }
@@ -345,8 +361,8 @@ __device__ __forceinline__ void sub_adjoint_lds(const Grid& g, const Model& md, 
 // workgroup barriers per step order the same accesses.
 template <int NTR, bool TANGENT, int KMAX, int TPB, int SN = 0, bool QL = false>
 __global__ __launch_bounds__(TPB, 1) void k_year_persistent(
-    Grid g, Model md, Mats mt, Persist ps, StepRange sr, double dtd, const double* __restrict__ y_in,
-    double* __restrict__ y_out, const double* __restrict__ v_in, double* __restrict__ v_out) {
+    Grid g, Model md, Mats mt, Persist ps, StepRange sr, double dtd, int slot0, StateView yin, StateView yout,
+    StateView vin, StateView vout) {
     constexpr int TV = TANGENT ? NTR : 1;
     constexpr bool SUB = SN > 0;
     __shared__ double s_red[TPB];
@@ -372,7 +388,18 @@ __global__ __launch_bounds__(TPB, 1) void k_year_persistent(
     const bool wave_local = ps.wave_local != 0;
 
     const int tid = threadIdx.x;
+    // the members of a launch run independently, gridDim.x workgroups each
+    const int ms = blockIdx.y;
     const int d = ps.block_dom[blockIdx.x];
+    ps.ring += (size_t)ms * ps.ring_len;
+    ps.vring += (size_t)ms * ps.ring_len;
+    ps.flags += ms * gridDim.x;
+    if (sr.store) sr.store += (size_t)ms * sr.store_step;
+    const double* const y_in = member_of(yin, ms);
+    double* const y_out = member_of(yout, ms);
+    const double* const v_in = TANGENT ? member_of(vin, ms) : nullptr;
+    double* const v_out = TANGENT ? member_of(vout, ms) : nullptr;
+    const double* const obs = sr.obs.p ? member_of(sr.obs, ms) : nullptr;
     const int c0 = ps.dom_col[d], c1 = ps.dom_col[d + 1];
     const int r0 = g.col_start[c0];
     const int nrows = g.col_start[c1] - r0;
@@ -407,8 +434,8 @@ __global__ __launch_bounds__(TPB, 1) void k_year_persistent(
     const size_t blk = (size_t)g.blk_off[c];
     const int latrow = g.col_lat[c];
 
-    // biogeochemical constants of this row (member 0 of the state)
-    const int m = md.member[0];
+    // biogeochemical constants of this row
+    const int m = md.member[slot0 + ms];
     const BgcParams p = load_params(md.u, md.model, md.nparam, m);
     const double rho = md.rho[((size_t)m * (g.nlayer + 1) + nc) * g.nlayer + k];
     const int ne = nc < g.neu ? nc : g.neu;
@@ -451,10 +478,10 @@ __global__ __launch_bounds__(TPB, 1) void k_year_persistent(
     double yr[NTR], vr[TV];
 #pragma unroll
     for (int t = 0; t < NTR; ++t) {
-        yr[t] = own ? y_in[(size_t)r * NTR + t] : 0.0;
+        yr[t] = own ? y_in[(size_t)r * yin.ld + t] : 0.0;
         s_y0[tid * NTR + t] = yr[t];
         if (TANGENT) {
-            vr[t % TV] = own ? v_in[(size_t)r * NTR + t] : 0.0;
+            vr[t % TV] = own ? v_in[(size_t)r * vin.ld + t] : 0.0;
             s_v0[tid * TV + t % TV] = vr[t % TV];
         }
     }
@@ -529,7 +556,6 @@ __global__ __launch_bounds__(TPB, 1) void k_year_persistent(
             m0 = k0;
             m1 = k1;
         }
-        const double om = 1.0 - w;
 
         // sources from the domain's own rows (no wait needed)
         double q[NTR], qd[TV];
@@ -576,22 +602,34 @@ __global__ __launch_bounds__(TPB, 1) void k_year_persistent(
                 if (e < ne) {
                     const double N = s_y[(lr0 + e) * NTR];
                     const Production pr = production(p, N, Q, light[e]);
-                    Phi += hz[e] * pr.f;
+                    Phi = __builtin_fma(hz[e], pr.f, Phi);
                     if (e == k) fk = pr.f;
                     if (TANGENT) {
                         const double fd = pr.dfdN * s_v[(lr0 + e) * TV];
-                        Phid += hz[e] * fd;
+                        Phid = __builtin_fma(hz[e], fd, Phid);
                         if (e == k) fdk = fd;
                     }
                 }
             }
             const double dop = NTR > 1 ? yr[NTR - 1] : 0.0;
-            q[0] = -fk + p.lam * dop + (1.0 - p.sig) * Phi * rho;
-            if (NTR > 1) q[NTR - 1] = p.sig * fk - p.lam * dop;
+            double q2;
+            row_q(p, fk, dop, Phi, rho, q[0], q2);
+            if (NTR > 1) q[NTR - 1] = q2;
             if (TANGENT) {
                 const double dopd = NTR > 1 ? vr[TV - 1] : 0.0;
-                qd[0] = -fdk + p.lam * dopd + (1.0 - p.sig) * Phid * rho;
-                if (NTR > 1) qd[TV - 1] = p.sig * fdk - p.lam * dopd;
+                row_q(p, fdk, dopd, Phid, rho, qd[0], q2);
+                if (NTR > 1) qd[TV - 1] = q2;
+            }
+        }
+
+        // formed here, before the halo wait: the compiler would otherwise sink
+        // the arithmetic to its use after the wait, on the path to the publish
+        if constexpr (!SUB) {
+#pragma unroll
+            for (int t = 0; t < NTR; ++t) asm volatile("" : "+v"(q[t]));
+            if constexpr (TANGENT) {
+#pragma unroll
+                for (int t = 0; t < TV; ++t) asm volatile("" : "+v"(qd[t]));
             }
         }
 
@@ -712,17 +750,17 @@ __global__ __launch_bounds__(TPB, 1) void k_year_persistent(
             if constexpr (!SUB && NTR <= 2) __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
             for (int s = 0; s < kEllMax; ++s) {
-                const double a = om * R.e0[s] + w * R.e1[s];
+                const double a = lerp(R.e0[s], R.e1[s], w);
 #pragma unroll
                 for (int t = 0; t < NTR; ++t) {
-                    acc[t] += a * yy[s][t];
-                    if (TANGENT) accd[t % TV] += a * vv[s][t % TV];
+                    acc[t] = __builtin_fma(a, yy[s][t], acc[t]);
+                    if (TANGENT) accd[t % TV] = __builtin_fma(a, vv[s][t % TV], accd[t % TV]);
                 }
             }
 #pragma unroll
             for (int t = 0; t < NTR; ++t) {
-                s_z[tid * NTR + t] = acc[t] + sc * q[t];
-                if (TANGENT) s_zd[tid * TV + t % TV] = accd[t % TV] + sc * qd[t % TV];
+                s_z[tid * NTR + t] = __builtin_fma(sc, q[t], acc[t]);
+                if (TANGENT) s_zd[tid * TV + t % TV] = __builtin_fma(sc, qd[t % TV], accd[t % TV]);
             }
         }
         if (wave_local) wave_lds_sync();       // the column's z: written by this wavefront
@@ -758,17 +796,17 @@ __global__ __launch_bounds__(TPB, 1) void k_year_persistent(
                 __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
                 for (int s = 0; s < KMAX; ++s) {
-                    const double a = om * R.a0[s] + w * R.a1[s];
+                    const double a = lerp(R.a0[s], R.a1[s], w);
 #pragma unroll
                     for (int t = 0; t < NTR; ++t) {
-                        acc[t] += a * zz[s][t];
-                        if (TANGENT) accd[t % TV] += a * zzd[s][t % TV];
+                        acc[t] = __builtin_fma(a, zz[s][t], acc[t]);
+                        if (TANGENT) accd[t % TV] = __builtin_fma(a, zzd[s][t % TV], accd[t % TV]);
                     }
                 }
             } else if constexpr (!SUB) {
 #pragma unroll
                 for (int s = 0; s < KMAX; ++s) {
-                    const double a = om * R.a0[s] + w * R.a1[s];
+                    const double a = lerp(R.a0[s], R.a1[s], w);
 #pragma unroll
                     for (int t = 0; t < NTR; ++t) {
                         acc[t] += a * zc[s * NTR + t];
@@ -778,7 +816,7 @@ __global__ __launch_bounds__(TPB, 1) void k_year_persistent(
             } else {
 #pragma unroll
                 for (int s = 0; s < KMAX; ++s) {
-                    const double a = om * R.a0[s] + w * R.a1[s];
+                    const double a = lerp(R.a0[s], R.a1[s], w);
                     const int ls = lr0 + (s < nc ? s : nc - 1);
 #pragma unroll
                     for (int t = 0; t < NTR; ++t) {
@@ -793,13 +831,13 @@ __global__ __launch_bounds__(TPB, 1) void k_year_persistent(
                 s_yn[tid * NTR + t] = acc[t];
                 // agent-scope stores write through the XCD's L2 to the point
                 // where every domain's loads see them
-                if (last) y_out[(size_t)r * NTR + t] = acc[t];
+                if (last) y_out[(size_t)r * yout.ld + t] = acc[t];
                 else __hip_atomic_store(&ps.ring[ring_at(wb, g.n, r, t)], publishable(acc[t]), __ATOMIC_RELAXED,
                                         __HIP_MEMORY_SCOPE_AGENT);
                 if (TANGENT) {
                     vr[t % TV] = accd[t % TV];
                     s_vn[tid * TV + t % TV] = accd[t % TV];
-                    if (last) v_out[(size_t)r * NTR + t] = accd[t % TV];
+                    if (last) v_out[(size_t)r * vout.ld + t] = accd[t % TV];
                     else __hip_atomic_store(&ps.vring[ring_at(wb, g.n, r, t)], publishable(accd[t % TV]),
                                             __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                 }
@@ -837,13 +875,13 @@ __global__ __launch_bounds__(TPB, 1) void k_year_persistent(
         if (wave_local) wave_lds_sync();
         else __syncthreads();
         // month-end misfit partial sums (after publishing, off the neighbours' critical path)
-        if (sr.obs && month_end) {
+        if (obs && month_end) {
             const int mo = (j + 1) / spm - 1;
             double cval = 0.0;
             if (own) {
 #pragma unroll
                 for (int t = 0; t < NTR; ++t) {
-                    const double dd = yr[t] - sr.obs[(size_t)mo * state_len + (size_t)r * NTR + t];
+                    const double dd = yr[t] - obs[(size_t)mo * sr.obs_month + (size_t)r * sr.obs.ld + t];
                     cval += vol * dd * dd;
                 }
             }
@@ -853,7 +891,7 @@ __global__ __launch_bounds__(TPB, 1) void k_year_persistent(
                 if (tid < hh) s_red[tid] += s_red[tid + hh];
                 __syncthreads();
             }
-            if (tid == 0) sr.jpart[(size_t)mo * gridDim.x + d] = s_red[0];
+            if (tid == 0) sr.jpart[((size_t)mo * gridDim.x + d) * sr.jpart_ld + ms] = s_red[0];
         }
     }
 }
@@ -891,9 +929,9 @@ __device__ __forceinline__ double column_sum(const double* v, int lr0, int nc) {
 // ---------------------------------------------------------------------------
 template <int NTR, int KMAX, int TPB, int SN = 0>
 __global__ __launch_bounds__(TPB, 1) void k_adjoint_persistent(
-    Grid g, Model md, Mats mt, Persist ps, double dtd, int j_lo, int j_hi,
-    const double* __restrict__ ystore, const double* __restrict__ obs, double src_scale,
-    const double* __restrict__ mu_in, double* __restrict__ mu_out, double* __restrict__ ubar_dom) {
+    Grid g, Model md, Mats mt, Persist ps, double dtd, int slot0, int j_lo, int j_hi, const double* ystore,
+    size_t ystore_step, StateView obsv, size_t obs_month, double src_scale, StateView muin, StateView muout,
+    double* __restrict__ ubar_dom, int ubar_ld) {
     constexpr int NP = NTR == 3 ? 11 : (NTR == 2 ? 7 : 5);
     constexpr bool SUB = SN > 0;
     __shared__ short s_rowcol[TPB];
@@ -921,7 +959,14 @@ __global__ __launch_bounds__(TPB, 1) void k_adjoint_persistent(
     __shared__ double s_sphi[TS];
 
     const int tid = threadIdx.x;
+    const int ms = blockIdx.y;                    // member of the launch
     const int d = ps.block_dom[blockIdx.x];
+    ps.ring += (size_t)ms * ps.ring_len;
+    ps.flags += ms * gridDim.x;
+    ystore += (size_t)ms * ystore_step;
+    const double* const mu_in = member_of(muin, ms);
+    double* const mu_out = member_of(muout, ms);
+    const double* const obs = obsv.p ? member_of(obsv, ms) : nullptr;
     const int c0 = ps.dom_col[d], c1 = ps.dom_col[d + 1];
     const int r0 = g.col_start[c0];
     const int nrows = g.col_start[c1] - r0;
@@ -951,7 +996,7 @@ __global__ __launch_bounds__(TPB, 1) void k_adjoint_persistent(
     const int spm = g.nstep / g.nmat;
     const double vol = g.area[c] * g.dz[k];
 
-    const int m = md.member[0];
+    const int m = md.member[slot0 + ms];
     const BgcParams p = load_params(md.u, md.model, md.nparam, m);
     const size_t tab = ((size_t)m * (g.nlayer + 1) + nc) * g.nlayer;
     const double rho = md.rho[tab + k];
@@ -1017,7 +1062,7 @@ __global__ __launch_bounds__(TPB, 1) void k_adjoint_persistent(
     double mr[NTR];
 #pragma unroll
     for (int t = 0; t < NTR; ++t) {
-        mr[t] = own ? mu_in[(size_t)r * NTR + t] : 0.0;
+        mr[t] = own ? mu_in[(size_t)r * muin.ld + t] : 0.0;
         s_mu[tid * NTR + t] = mr[t];
     }
     s_rmu[tid] = rhoc * mr[0];
@@ -1254,7 +1299,7 @@ __global__ __launch_bounds__(TPB, 1) void k_adjoint_persistent(
 #pragma unroll
             for (int t = 0; t < NTR; ++t) {
                 lam[t] += (SUB ? 1.0 : dtd) * ybar[t];
-                if (mo >= 0) lam[t] += vol * (yj[t] - obs[(size_t)mo * state_len + (size_t)r * NTR + t]) * src_scale;
+                if (mo >= 0) lam[t] += vol * (yj[t] - obs[(size_t)mo * obs_month + (size_t)r * obsv.ld + t]) * src_scale;
                 s_lam[tid * NTR + t] = lam[t];
             }
         }
@@ -1286,7 +1331,7 @@ __global__ __launch_bounds__(TPB, 1) void k_adjoint_persistent(
             for (int t = 0; t < NTR; ++t) {
                 mr[t] = out[t];
                 s_mu[tid * NTR + t] = out[t];
-                if (last) mu_out[(size_t)r * NTR + t] = out[t];
+                if (last) mu_out[(size_t)r * muout.ld + t] = out[t];
                 else __hip_atomic_store(&ps.ring[ring_at(wb, g.n, r, t)], publishable(out[t]), __ATOMIC_RELAXED,
                                         __HIP_MEMORY_SCOPE_AGENT);
             }
@@ -1321,12 +1366,12 @@ __global__ __launch_bounds__(TPB, 1) void k_adjoint_persistent(
             if (tid < hh) s_red[tid] += s_red[tid + hh];
             __syncthreads();
         }
-        if (tid == 0) ubar_dom[(size_t)d * NP + q] += (SUB ? md.hsub : dtd) * s_red[0];
+        if (tid == 0) ubar_dom[((size_t)d * ubar_ld + ms) * NP + q] += (SUB ? md.hsub : dtd) * s_red[0];
         __syncthreads();
     }
 }
 
-__global__ void k_fill_int(int* __restrict__ x, int len, int value) {
+[[maybe_unused]] static __global__ void k_fill_int(int* __restrict__ x, int len, int value) {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i < len) x[i] = value;
 }

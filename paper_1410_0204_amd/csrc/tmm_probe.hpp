@@ -26,7 +26,7 @@ __device__ __forceinline__ int xcc_id() {
 // r to word 1.  Stores and polls are the persistent kernels' (relaxed, agent
 // scope, one s_sleep between polls).  out[0] = ticks of a's loop, out[1..2] =
 // the XCDs a and b ran on.  words[0] and words[kProbeWordStride] must be 0.
-__global__ void k_probe_pingpong(int a, int b, int rounds, long long* __restrict__ words,
+[[maybe_unused]] static __global__ void k_probe_pingpong(int a, int b, int rounds, long long* __restrict__ words,
                                  long long* __restrict__ out, int* __restrict__ fail) {
     if ((int)blockIdx.x != a && (int)blockIdx.x != b) return;
     if (threadIdx.x != 0) return;
@@ -69,7 +69,7 @@ __global__ __launch_bounds__(TPB) void k_probe_barrier(int n, long long* __restr
 
 // A chain of n dependent agent-scope loads through next[] (a cycle over
 // distinct 256-byte lines).  out[0] = ticks.
-__global__ void k_probe_load(int n, const int* __restrict__ next, long long* __restrict__ out) {
+[[maybe_unused]] static __global__ void k_probe_load(int n, const int* __restrict__ next, long long* __restrict__ out) {
     if (threadIdx.x != 0) return;
     int i = 0;
     const long long t0 = wall_clock64();
@@ -78,7 +78,7 @@ __global__ void k_probe_load(int n, const int* __restrict__ next, long long* __r
 }
 
 // next[l * 64] = ((l + step) % nlines) * 64: a cycle over nlines lines of 256 bytes.
-__global__ void k_probe_chain(int nlines, int step, int* __restrict__ next) {
+[[maybe_unused]] static __global__ void k_probe_chain(int nlines, int step, int* __restrict__ next) {
     const int l = blockIdx.x * blockDim.x + threadIdx.x;
     if (l < nlines) next[(size_t)l * 64] = ((l + step) % nlines) * 64;
 }
