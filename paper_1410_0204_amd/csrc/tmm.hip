@@ -323,7 +323,7 @@ int validate(const tmm_desc* d, Plan& P) {
     P.o_pdepidx = take(P.dep_capacity * 4);
     P.o_pflags = take((size_t)kMaxDomains * 4);     // domains x members of a launch
     P.o_pabort = take(64);
-    P.o_finite = take(64);
+    P.o_finite = take(64);                          // (take_flags reads both in one copy)
     P.o_probe = take(kProbeBytes);
     P.o_phaloptr = take((size_t)(kMaxDomains + 1) * 4);
     P.halo_capacity = (size_t)d->ae_nnz + 1;
@@ -364,6 +364,7 @@ struct tmm_ctx {
     int nbatch = 0;            // members set by tmm_set_params
     double vtot = 0.0;         // total wet volume
     std::vector<int> h_member, h_scol, h_dcol;
+    bool map_is_identity = false;  // the device's member map is 0, 1, 2, ... (as tmm_set_params leaves it)
     std::vector<double> h_vec;
     // persistent year kernel
     bool pers_ok = false;          // tables built and the launch fits the device
@@ -1025,33 +1026,29 @@ bool single_launch(const tmm_ctx* h, int nb, bool derivative) {
     return groups <= (h->bins ? 6 + h->P.n / 10000 : 4);
 }
 
-// After the persistent launches of a call: a set abort flag means a wait
-// gave up in one of them.  It is reported once and cleared, so the next call
-// starts afresh.
-int check_abort(tmm_ctx* h) {
-    if (!h->pers_used) return TMM_OK;
-    int flag = 0;
-    TMM_TRY(hipMemcpyAsync(&flag, h->at<int>(h->P.o_pabort), 4, hipMemcpyDeviceToHost, h->stream));
+// After the launches of a call: a set abort flag means a wait of the persistent
+// kernels gave up, a set non-finite flag (read only if asked for) that some
+// year ended with a NaN or an infinity in its state.  Both come back in one
+// copy, are reported once and cleared, so the next call starts afresh.
+int take_flags(tmm_ctx* h, bool nonfinite) {
+    if (!h->pers_used && !nonfinite) return TMM_OK;
+    constexpr size_t step = kAlign / 4;                  // the two words' distance (see plan: o_pabort, o_finite)
+    int flag[step + 1];
+    TMM_TRY(hipMemcpyAsync(flag, h->at<int>(h->P.o_pabort), sizeof(flag), hipMemcpyDeviceToHost, h->stream));
     TMM_TRY(hipStreamSynchronize(h->stream));
+    const bool gave_up = h->pers_used && flag[0], bad = nonfinite && flag[step];
     h->pers_used = false;
-    if (!flag) return TMM_OK;
-    hipLaunchKernelGGL(tmm::k_fill_int, dim3(1), dim3(64), 0, h->stream, h->at<int>(h->P.o_pabort), 16, 0);
-    TMM_LAUNCHED();
+    if (!gave_up && !bad) return TMM_OK;
+    if (gave_up) {
+        hipLaunchKernelGGL(tmm::k_fill_int, dim3(1), dim3(64), 0, h->stream, h->at<int>(h->P.o_pabort), 16, 0);
+        TMM_LAUNCHED();
+    }
+    if (nonfinite && flag[step]) {
+        hipLaunchKernelGGL(tmm::k_fill_int, dim3(1), dim3(64), 0, h->stream, h->at<int>(h->P.o_finite), 16, 0);
+        TMM_LAUNCHED();
+    }
     TMM_TRY(hipStreamSynchronize(h->stream));
-    return TMM_EDEVICE;
-}
-
-// After the model years of a call: a set non-finite flag means some year
-// ended with a NaN or an infinity in its state.  Reported once and cleared.
-int take_nonfinite(tmm_ctx* h) {
-    int flag = 0;
-    TMM_TRY(hipMemcpyAsync(&flag, h->at<int>(h->P.o_finite), 4, hipMemcpyDeviceToHost, h->stream));
-    TMM_TRY(hipStreamSynchronize(h->stream));
-    if (!flag) return TMM_OK;
-    hipLaunchKernelGGL(tmm::k_fill_int, dim3(1), dim3(64), 0, h->stream, h->at<int>(h->P.o_finite), 16, 0);
-    TMM_LAUNCHED();
-    TMM_TRY(hipStreamSynchronize(h->stream));
-    return TMM_ENONFINITE;
+    return gave_up ? TMM_EDEVICE : TMM_ENONFINITE;
 }
 
 // One model year of the launch-per-step path replayed from a hipGraph: the
@@ -1615,8 +1612,7 @@ int sqdiff(tmm_ctx* h, int nb, const double* a, const double* b, int volume, dou
     TMM_LAUNCHED();
     (void)part_stride_tiles;
     if (out) {
-        hipLaunchKernelGGL(tmm::k_sum_tiles, dim3(1), dim3(256), 0, h->stream, t.ntile, nb, nb, pp, scale,
-                           accumulate, take_sqrt, out);
+        hipLaunchKernelGGL(tmm::k_sum_tiles, dim3(nb), dim3(256), 0, h->stream, t.ntile, nb, pp, scale, accumulate, take_sqrt, out);
         TMM_LAUNCHED();
     }
     return TMM_OK;
@@ -1666,8 +1662,7 @@ int adjoint_persistent(tmm_ctx* h, int nb, const double* y0, const double* obs, 
         tmm::StepRange fl{lo_last, P.nstep, seg + (size_t)s * seg_step, 1, seg_step, ob, len, jpart + s, nb};
         if ((rc = launch_persistent(h, M, s, fl, from, batch_view(h, fin, W, s)))) return rc;
     }
-    hipLaunchKernelGGL(tmm::k_sum_tiles, dim3(1), dim3(256), 0, h->stream, P.nmat * G, nb, nb, jpart, 0.5 * scale, 0, 0,
-                       h->vec(4));
+    hipLaunchKernelGGL(tmm::k_sum_tiles, dim3(nb), dim3(256), 0, h->stream, P.nmat * G, nb, jpart, 0.5 * scale, 0, 0, h->vec(4));
     TMM_LAUNCHED();
     // head: lambda_nstep = source of the last month, mu_{nstep-1} = Ai(t_{nstep-1})^T lambda_nstep
     {
@@ -1714,14 +1709,13 @@ int adjoint_persistent(tmm_ctx* h, int nb, const double* y0, const double* obs, 
             im = 1 - im;
         }
     }
-    hipLaunchKernelGGL(tmm::k_sum_tiles, dim3(1), dim3(256), 0, h->stream, G, nb * np, nb * np, ubar, 1.0, 0, 0,
-                       h->vec(5));
+    hipLaunchKernelGGL(tmm::k_sum_tiles, dim3(nb * np), dim3(256), 0, h->stream, G, nb * np, ubar, 1.0, 0, 0, h->vec(5));
     TMM_LAUNCHED();
     std::vector<double> J(nb), Gr((size_t)nb * np);
     TMM_TRY(hipMemcpyAsync(J.data(), h->vec(4), (size_t)nb * 8, hipMemcpyDeviceToHost, h->stream));
     TMM_TRY(hipMemcpyAsync(Gr.data(), h->vec(5), (size_t)nb * np * 8, hipMemcpyDeviceToHost, h->stream));
     TMM_TRY(hipStreamSynchronize(h->stream));
-    if ((rc = check_abort(h))) return rc;
+    if ((rc = take_flags(h, false))) return rc;
     for (int b = 0; b < nb; ++b) {
         if (!std::isfinite(J[b])) return TMM_ENONFINITE;
         J_host[b] = J[b];
@@ -1912,8 +1906,7 @@ int tmm_create(const tmm_desc* d, void* dev_workspace, size_t bytes, void* hip_s
         tmm::Grid g = h->grid(t);
         hipLaunchKernelGGL((tmm::k_tile_volume<kMaxTileRows, kMaxTileRows>), dim3(t.ntile), dim3(256), 0,
                            h->stream, g, h->part());
-        hipLaunchKernelGGL(tmm::k_sum_tiles, dim3(1), dim3(64), 0, h->stream, t.ntile, 1, 1, h->part(), 1.0, 0, 0,
-                           h->vec(15));
+        hipLaunchKernelGGL(tmm::k_sum_tiles, dim3(1), dim3(256), 0, h->stream, t.ntile, 1, h->part(), 1.0, 0, 0, h->vec(15));
         if (hipGetLastError() != hipSuccess) return fail(TMM_EDEVICE);
         if (hipMemcpyAsync(&h->vtot, h->vec(15), 8, hipMemcpyDeviceToHost, h->stream) != hipSuccess)
             return fail(TMM_EDEVICE);
@@ -1953,6 +1946,7 @@ int tmm_set_params(tmm_handle h, int nbatch, const double* u) {
     if (upload(h, h->at<double>(h->P.o_uT), ut.data(), ut.size() * 8)) return TMM_EDEVICE;
     for (int b = 0; b < nbatch; ++b) h->h_member[b] = b;
     if (upload(h, h->at<int>(h->P.o_member), h->h_member.data(), (size_t)nbatch * 4)) return TMM_EDEVICE;
+    h->map_is_identity = true;
     const int total = nbatch * (h->P.nlayer + 1) * h->P.nlayer;
     hipLaunchKernelGGL(tmm::k_param_tables, dim3((total + 255) / 256), dim3(256), 0, h->stream, nbatch, h->P.model,
                        np, h->P.nlayer, h->P.neu, h->at<double>(h->P.o_u), h->at<double>(h->P.o_dz),
@@ -1972,6 +1966,10 @@ int tmm_step(tmm_handle h, int j, const double* y_in, double* y_out) {
 
 // Member map: slot s of the working state holds member h_member[s].
 static int push_member_map(tmm_handle h, int na) {
+    bool identity = true;
+    for (int s = 0; s < na; ++s) identity = identity && h->h_member[s] == s;
+    if (identity && h->map_is_identity) return TMM_OK;
+    h->map_is_identity = identity && na == h->nbatch;
     if (upload(h, h->at<int>(h->P.o_member), h->h_member.data(), (size_t)na * 4)) return TMM_EDEVICE;
     TMM_TRY(hipStreamSynchronize(h->stream));
     return TMM_OK;
@@ -2008,6 +2006,7 @@ int tmm_year(tmm_handle h, int nyears, const int* years_per_member, const double
             ++k;
         }
         if (!k) return TMM_OK;
+        if (k == nb && Wc == Wf) return copy(h, y1, h->ybuf(ib), n * Wf);    // every member, in its place
         if (upload(h, h->at<int>(h->P.o_scol), h->h_scol.data(), (size_t)k * 4) ||
             upload(h, h->at<int>(h->P.o_dcol), h->h_dcol.data(), (size_t)k * 4))
             return TMM_EDEVICE;
@@ -2103,8 +2102,7 @@ int tmm_year(tmm_handle h, int nyears, const int* years_per_member, const double
     // restore the identity member map for later calls
     for (int b = 0; b < nb; ++b) h->h_member[b] = b;
     if ((rc = push_member_map(h, nb))) return rc;
-    if ((rc = check_abort(h))) return rc;
-    return take_nonfinite(h);
+    return take_flags(h, true);
 }
 
 int tmm_year_jvp(tmm_handle h, int mode, const double* y, const double* v, double* phi_y, double* jv) {
@@ -2118,7 +2116,7 @@ int tmm_year_jvp(tmm_handle h, int mode, const double* y, const double* v, doubl
     double* f0 = phi_y ? phi_y : h->ybuf(2);
     if (mode == TMM_JVP_TANGENT) {
         int rt = run_year(h, nb, y, f0, h->ybuf(0), h->ybuf(1), v, jv, h->vbuf(0), h->vbuf(1));
-        return rt ? rt : check_abort(h);
+        return rt ? rt : take_flags(h, false);
     }
     // finite differences: h_s = 1e-8 ||y_s|| / ||v_s||
     int rc = sqdiff(h, nb, y, nullptr, 0, 1.0, 0, h->vec(1));
@@ -2134,7 +2132,7 @@ int tmm_year_jvp(tmm_handle h, int mode, const double* y, const double* v, doubl
     hipLaunchKernelGGL(tmm::k_fd_quot, dim3(launch_blocks(n * W)), dim3(256), 0, h->stream, n, W, ntr, h->vec(3),
                        jv, f0, jv);
     TMM_LAUNCHED();
-    return check_abort(h);
+    return take_flags(h, false);
 }
 
 static int drop_graphs(tmm_handle h) {
@@ -2291,8 +2289,7 @@ int tmm_year_noalloc(tmm_handle h, int nyears, const double* y0, double* y1, dou
             hipLaunchKernelGGL((tmm::k_tile_sqdiff<kMaxTileRows, kMaxTileRows>), dim3(tf.ntile), dim3(256), 0,
                                h->stream, g, W, P.ntr, nb, y1, start, 0, part);
             TMM_LAUNCHED();
-            hipLaunchKernelGGL(tmm::k_sum_tiles, dim3(1), dim3(256), 0, h->stream, tf.ntile, nb, nb, part, 1.0, 0, 1,
-                               vec);
+            hipLaunchKernelGGL(tmm::k_sum_tiles, dim3(nb), dim3(256), 0, h->stream, tf.ntile, nb, part, 1.0, 0, 1, vec);
             TMM_LAUNCHED();
             TMM_TRY(hipMemcpyAsync(resid_host + (size_t)yr * nb, vec, (size_t)nb * 8, hipMemcpyDeviceToHost,
                                    h->stream));
@@ -2411,8 +2408,7 @@ int tmm_year_adjoint(tmm_handle h, const double* y0, const double* obs, int ckpt
             }
             cur = nxt;
         }
-        hipLaunchKernelGGL(tmm::k_sum_tiles, dim3(1), dim3(256), 0, h->stream, P.nmat * ntile_m, nb, nb, jpart,
-                           1.0 / (2.0 * P.nmat * h->vtot), 0, 0, h->vec(4));
+        hipLaunchKernelGGL(tmm::k_sum_tiles, dim3(nb), dim3(256), 0, h->stream, P.nmat * ntile_m, nb, jpart, 1.0 / (2.0 * P.nmat * h->vtot), 0, 0, h->vec(4));
         TMM_LAUNCHED();
     }
     const size_t lds = (size_t)tl.max_rows * W * 8 + (size_t)256 * np * 8;
@@ -2463,8 +2459,7 @@ int tmm_year_adjoint(tmm_handle h, const double* y0, const double* obs, int ckpt
     // tail: lambda_0 = Ae(t_0)^T mu_0 + dt_d (dq/dy)(y_0)^T mu_0
     double* l0 = dJdy0 ? dJdy0 : mu[1 - im];
     if ((rc = adjoint(0, 1, 0, mu[im], y0, nullptr, l0))) return rc;
-    hipLaunchKernelGGL(tmm::k_sum_tiles, dim3(1), dim3(256), 0, h->stream, tl.ntile, nb * np, nb * np, ubt, 1.0, 0, 0,
-                       h->vec(5));
+    hipLaunchKernelGGL(tmm::k_sum_tiles, dim3(nb * np), dim3(256), 0, h->stream, tl.ntile, nb * np, ubt, 1.0, 0, 0, h->vec(5));
     TMM_LAUNCHED();
     std::vector<double> J(nb), G((size_t)nb * np);
     TMM_TRY(hipMemcpyAsync(J.data(), h->vec(4), (size_t)nb * 8, hipMemcpyDeviceToHost, h->stream));
