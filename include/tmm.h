@@ -221,7 +221,10 @@ enum {
     TMM_OPT_TILE_ROWS = 9,       /* largest tile (rows per workgroup) of the launch-per-step tile
                                     kernels: 32, 64, 128 or 256 (a tiling no deeper than the
                                     deepest column is used as the smallest); 0 = by state width
-                                    (128 up to 4 state columns, else 256) */
+                                    (128 up to 4 state columns, else 256), and the streaming kernel
+                                    for one member's forward steps where it takes the grid (at most
+                                    24 layers and 5 explicit entries per row, one BGC evaluation
+                                    per step) */
     TMM_OPT_WAVE_LOCAL = 10,     /* 1 (default): the persistent kernels place each water column
                                     within 16 or 32 lanes of a wavefront (at most 32 layers, 5
                                     explicit entries per row, 256 rows per domain, and a domain for

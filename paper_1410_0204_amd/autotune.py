@@ -6,8 +6,8 @@ rounding order:
 
 * one member: the single-launch year kernel with several domain sizes (rows
   per workgroup; each domain is one workgroup of up to 256 or 512 rows), and
-  the launch-per-step tile kernel with each tile size (32 .. 256 rows per
-  workgroup);
+  the launch-per-step kernels: the streaming one where it runs, and the tile
+  kernel with each tile size (32 .. 256 rows per workgroup);
 * ensembles: the member-parallel kernel (one wavefront per water column,
   lane = member) with 2, 4 or 8 wavefronts per workgroup and its column order
   (bands of 4 .. 32 latitude rows swept by longitude, or the natural order),
@@ -74,6 +74,8 @@ def candidates(t, nbatch):
     if nbatch == 1 and t.query(T.TMM_Q_PERSISTENT):
         for rows in DOMAIN_ROWS:
             out.append({T.TMM_OPT_PERSISTENT: 1, T.TMM_OPT_DOMAIN_ROWS: rows})
+    if nbatch == 1:
+        out.append({T.TMM_OPT_PERSISTENT: 0, T.TMM_OPT_MEMBER_KERNEL_MIN: 0})
     for rows in TILE_ROWS:
         out.append({T.TMM_OPT_PERSISTENT: 0, T.TMM_OPT_MEMBER_KERNEL_MIN: 0, T.TMM_OPT_TILE_ROWS: rows})
     # the library's default crossover to the member kernel (see TMM_OPT_MEMBER_KERNEL_MIN)

@@ -744,6 +744,145 @@ __global__ __launch_bounds__(256) void k_step(Grid g, Model md, Mats mt, int W, 
 
 
 // ---------------------------------------------------------------------------
+// Forward step of one member on grids whose matrices stream from memory (one
+// BGC evaluation per step, at most kStreamLayers layers and kStreamEll
+// explicit entries per row): bound by the bytes of the month pair of Ai and
+// Ae (0.33 GB of the 0.35 GB a step of the 360x180x23 grid moves) on large
+// grids and by its chain of dependent loads on small ones.  k_step
+// reads the Ai blocks after the barrier that completes z, a few loads at a
+// time per lane; here a workgroup knows its tile's blocks as one contiguous
+// range and issues every load of it first (16 bytes per lane, both months,
+// consecutive lanes on consecutive words), so that they are in flight while z
+// is formed; the interpolated blocks go through LDS to the lanes that own the
+// rows.  What a lane needs to know of its row and tile comes from two host
+// tables, so that only one load precedes the streaming.
+//
+// One row per lane and 128 rows per workgroup: 24 KB of blocks and 48 KB of
+// them in flight; five workgroups share a compute unit.  Steps of the
+// 500000-point grid with the months in cache 48.0 -> 40.8 us (three tracers 77
+// -> 43.7), of the 52749-point grid 12.4 -> 5.9 (20.5 -> 6.4).
+//
+// tile[b]: first row, rows, first block word and block words of workgroup b;
+// row[r]: block offset of the row's column, and layer | depth << 8 | latitude
+// row << 16.
+// ---------------------------------------------------------------------------
+constexpr int kStreamRows = 128;        // rows (lanes) per workgroup
+constexpr int kStreamLayers = 24;
+constexpr int kStreamEll = 5;
+constexpr int kStreamPairs = kStreamRows * kStreamLayers / 2 / kStreamRows;   // 16-byte loads per lane and month
+
+template <int NTR>
+__global__ __launch_bounds__(kStreamRows) void k_step_stream(Grid g, Model md, Mats mt, int j, double dtd,
+                                                             const int4* __restrict__ tile,
+                                                             const uint2* __restrict__ row,
+                                                             const double* __restrict__ y, double* __restrict__ yo) {
+    typedef double d2 __attribute__((ext_vector_type(2)));
+    __shared__ __align__(16) double s_ai[kStreamRows * kStreamLayers];
+    __shared__ __align__(16) double s_z[(kStreamRows + kStreamLayers) * NTR];
+    __shared__ double s_f[kStreamRows];
+    const int tid = threadIdx.x;
+    const int4 tl = tile[blockIdx.x];
+    int k0, k1;
+    double w;
+    step_phase(j, g.nstep, g.nmat, k0, k1, w);
+
+    // the tile's blocks of both months (a range check in place of a branch:
+    // words past the tile read as zeros, the odd last one as its neighbour's)
+    const int bytes = (tl.w + 1) / 2 * 16;
+    const __amdgpu_buffer_rsrc_t b0 = __builtin_amdgcn_make_buffer_rsrc(
+        const_cast<double*>(mt.ai_cm + (size_t)k0 * mt.ai_month + tl.z), (short)0, bytes, 0x00020000);
+    const __amdgpu_buffer_rsrc_t b1 = __builtin_amdgcn_make_buffer_rsrc(
+        const_cast<double*>(mt.ai_cm + (size_t)k1 * mt.ai_month + tl.z), (short)0, bytes, 0x00020000);
+    d2 p0[kStreamPairs], p1[kStreamPairs];
+#pragma unroll
+    for (int i = 0; i < kStreamPairs; ++i) {
+        const int off = (i * kStreamRows + tid) * 16;
+        p0[i] = __builtin_bit_cast(d2, __builtin_amdgcn_raw_buffer_load_b128(b0, off, 0, 0));
+        p1[i] = __builtin_bit_cast(d2, __builtin_amdgcn_raw_buffer_load_b128(b1, off, 0, 0));
+    }
+
+    // the row: explicit entries, state, sources
+    const bool own = tid < tl.y;
+    const int r = tl.x + (own ? tid : 0);
+    const uint2 ri = row[r];
+    const int k = ri.y & 255, nc = ri.y >> 8 & 255;
+    const int lr0 = (own ? tid : 0) - k;                 // the column's first row in the tile
+    const double* const ae0 = mt.ae + (size_t)k0 * mt.ae_month;
+    const double* const ae1 = mt.ae + (size_t)k1 * mt.ae_month;
+    double a[kStreamEll], yy[kStreamEll][NTR];
+    int col[kStreamEll];
+#pragma unroll
+    for (int s = 0; s < kStreamEll; ++s) {
+        const bool in = s < mt.ew;
+        const size_t e = (size_t)(in ? s : 0) * g.npad + r;
+        col[s] = mt.ae_col[e];
+        a[s] = in ? lerp(ae0[e], ae1[e], w) : 0.0;
+    }
+#pragma unroll
+    for (int s = 0; s < kStreamEll; ++s)
+#pragma unroll
+        for (int t = 0; t < NTR; ++t) yy[s][t] = y[(size_t)col[s] * NTR + t];
+    const int m = md.member[0];
+    const BgcParams p = load_params(md.u, md.model, md.nparam, m);
+    const int ne = nc < g.neu ? nc : g.neu;
+    const double Q = g.ins[(size_t)(j % g.nstep) * g.nlat + (ri.y >> 16)];
+    const double rho = md.rho[((size_t)m * (g.nlayer + 1) + nc) * g.nlayer + k];
+    // entry 0 reads the row itself
+    double f = 0.0;
+    if (own && k < ne) {
+        f = production(p, yy[0][0], Q, md.light[(size_t)m * g.nlayer + k]).f;
+        if (NTR == 3) f *= yy[0][NTR - 1];
+    }
+    s_f[tid] = f;
+    if (tid < kStreamLayers * NTR) s_z[kStreamRows * NTR + tid] = 0.0;
+    __syncthreads();
+    double Phi = 0.0;
+    for (int e = 0; e < ne; ++e) Phi = __builtin_fma(g.dz[e], NTR == 3 ? p.sig3 * s_f[lr0 + e] : s_f[lr0 + e], Phi);
+    double q[NTR];
+    if constexpr (NTR == 3) {
+        const double D = yy[0][1], P = yy[0][2];
+        const double loss = k < ne ? p.lam3 * P + p.kap3 * P * P : 0.0;
+        q[0] = -f + p.lam * D + (1.0 - p.sig) * Phi * rho;
+        q[1] = p.sig * (p.sig3 * f) + loss - p.lam * D + p.lam3p * P;
+        q[2] = (1.0 - p.sig3) * f - loss - p.lam3p * P;
+    } else {
+        double q2;
+        row_q(p, f, NTR > 1 ? yy[0][NTR - 1] : 0.0, Phi, rho, q[0], q2);
+        if (NTR > 1) q[NTR - 1] = q2;
+    }
+#pragma unroll
+    for (int t = 0; t < NTR; ++t) {
+        double z = 0.0;
+#pragma unroll
+        for (int s = 0; s < kStreamEll; ++s) z = __builtin_fma(a[s], yy[s][t], z);
+        s_z[tid * NTR + t] = own ? __builtin_fma(dtd, q[t], z) : 0.0;
+    }
+#pragma unroll
+    for (int i = 0; i < kStreamPairs; ++i) {
+        d2 v;
+        v.x = lerp(p0[i].x, p1[i].x, w);
+        v.y = lerp(p0[i].y, p1[i].y, w);
+        *reinterpret_cast<d2*>(s_ai + (i * kStreamRows + tid) * 2) = v;
+    }
+    __syncthreads();
+    if (!own) return;
+    double acc[NTR];
+#pragma unroll
+    for (int t = 0; t < NTR; ++t) acc[t] = 0.0;
+    const double* const ab = s_ai + ((int)ri.x - tl.z) + k;
+    const double* const zb = s_z + (size_t)lr0 * NTR;
+#pragma unroll 4
+    for (int s = 0; s < nc; ++s) {
+        const double c = ab[s * nc];
+#pragma unroll
+        for (int t = 0; t < NTR; ++t) acc[t] = __builtin_fma(c, zb[s * NTR + t], acc[t]);
+    }
+#pragma unroll
+    for (int t = 0; t < NTR; ++t) yo[(size_t)r * NTR + t] = acc[t];
+}
+
+
+// ---------------------------------------------------------------------------
 // Forward step for ensembles: one wavefront per water column and group of up
 // to 64 members, lane = member (both tracers).  Each wavefront first stages
 // the column's interpolated matrices in its own LDS slice with coalesced loads
