@@ -366,7 +366,7 @@ def main():
     torch.cuda.synchronize()
 
     persistent = bool(t.query(tmm.TMM_Q_PERSISTENT))
-    kernel = "k_year_persistent" if persistent else "k_step"
+    kernel = "k_year_bins" if persistent else "k_step_stream"
     log(f"[bench] path: {kernel}" + (f" ({t.query(tmm.TMM_Q_DOMAINS)} domains on "
                                      f"{t.query(tmm.TMM_Q_COMPUTE_UNITS)} CUs)" if persistent else ""))
 
@@ -557,8 +557,8 @@ def bench_variant(args, inp, dev, stream, ms_plain, label):
     ms_adj = start.elapsed_time(stop)
     rec = {"ms_per_year": ms_fwd, "model_years_per_s": 1000.0 / ms_fwd,
            "cost_vs_headline": ms_fwd / ms_plain, "adjoint_ms": ms_adj, "adjoint_forward_ratio": ms_adj / ms_fwd,
-           "forward_path": "k_year_persistent" if t.query(tmm.TMM_Q_PERSISTENT) else "k_step",
-           "adjoint_path": "k_adjoint_persistent" if t.query(tmm.TMM_Q_PERSISTENT_ADJOINT) else "k_adjoint",
+           "forward_path": "k_year_bins" if t.query(tmm.TMM_Q_PERSISTENT) else "k_step_stream",
+           "adjoint_path": "k_adjoint_bins" if t.query(tmm.TMM_Q_PERSISTENT_ADJOINT) else "k_adjoint",
            "adjoint_ckpt_every": inp.nstep}
     log(f"[bench] {label}: {ms_fwd:.3f} ms/model-year ({ms_fwd / ms_plain:.2f}x), "
         f"adjoint {ms_adj:.2f} ms (ratio {ms_adj / ms_fwd:.2f}, {rec['adjoint_path']})")
@@ -591,7 +591,7 @@ def bench_copy(args):
 
 
 def bench_grids(args):
-    """Launch-per-step model years (graph-replayed k_step, one member, N-DOP) on the
+    """Launch-per-step model years (graph-replayed k_step_stream, one member, N-DOP) on the
     global 128x64x15, the 256x128x23 and the 1.0-degree 360x180x23 grids: how the
     achieved bandwidth of the step kernel scales with the grid.  On the larger
     grids the month pair of matrices no longer fits the 256 MB Infinity Cache and
@@ -653,7 +653,7 @@ def bench_grids(args):
         t.close()
         del t
         torch.cuda.empty_cache()
-    print(json.dumps({"mode": "grids", "kernel": "k_step (graph-replayed, one launch per step)", "rows": rows}),
+    print(json.dumps({"mode": "grids", "kernel": "k_step_stream (graph-replayed, one launch per step)", "rows": rows}),
           flush=True)
 
 
