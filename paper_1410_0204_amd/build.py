@@ -10,7 +10,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 LIB = os.path.join(HERE, "libtmm.so")
 UNITS = ("tmm.hip", "tmm_bins_1.hip", "tmm_bins_2.hip", "tmm_bins_3.hip")
-PARTS = ("tmm_device.hpp", "tmm_persistent.hpp", "tmm_bins.hpp", "tmm_substep.hpp", "tmm_probe.hpp")
+PARTS = ("tmm_rules.hpp", "tmm_device.hpp", "tmm_persistent.hpp", "tmm_bins.hpp", "tmm_substep.hpp", "tmm_probe.hpp")
 SOURCES = [os.path.join(HERE, "csrc", f) for f in UNITS]
 HEADERS = [os.path.join(HERE, "csrc", f) for f in PARTS] + [os.path.join(ROOT, "include", "tmm.h")]
 

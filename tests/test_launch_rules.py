@@ -1,0 +1,37 @@
+"""The library's integer layout and launch rules (csrc/tmm_rules.hpp), compiled for the host."""
+
+import ctypes
+import os
+import subprocess
+
+import pytest
+
+CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_1410_0204_amd", "csrc")
+
+SHIM = r"""
+#include "tmm_rules.hpp"
+extern "C" {
+int bins_cells(int halo_max) { return tmm::bins_cells(halo_max); }
+int bins_buffer_bytes(int halo_max, int ntr) { return tmm::bins_buffer_bytes(halo_max, ntr); }
+}
+"""
+
+
+@pytest.fixture(scope="module")
+def rules(tmp_path_factory):
+    d = tmp_path_factory.mktemp("rules")
+    src, out = d / "rules.cpp", d / "librules.so"
+    src.write_text(SHIM)
+    subprocess.run(["g++", "-std=c++17", "-O1", "-Wall", "-Werror", "-fPIC", "-shared", "-I", CSRC, "-o", str(out),
+                    str(src)], check=True)
+    return ctypes.CDLL(str(out))
+
+
+@pytest.mark.parametrize("ntr", [1, 2, 3])
+def test_binned_lds_buffers_start_on_16_bytes(rules, ntr):
+    """The binned kernels keep two buffers one after the other in LDS and access their cells as 16-byte
+    vectors: whatever the halo of a grid's domains, a buffer holds it and ends on 16 bytes."""
+    for halo in range(0, 513):
+        assert rules.bins_cells(halo) >= 256 + halo
+        assert rules.bins_buffer_bytes(halo, ntr) == rules.bins_cells(halo) * ntr * 8
+        assert rules.bins_buffer_bytes(halo, ntr) % 16 == 0, halo
