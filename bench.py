@@ -366,7 +366,7 @@ def main():
     torch.cuda.synchronize()
 
     persistent = bool(t.query(tmm.TMM_Q_PERSISTENT))
-    kernel = "k_year_bins" if persistent else "k_step_stream"
+    kernel = year_kernel(t)
     log(f"[bench] path: {kernel}" + (f" ({t.query(tmm.TMM_Q_DOMAINS)} domains on "
                                      f"{t.query(tmm.TMM_Q_COMPUTE_UNITS)} CUs)" if persistent else ""))
 
@@ -557,13 +557,28 @@ def bench_variant(args, inp, dev, stream, ms_plain, label):
     ms_adj = start.elapsed_time(stop)
     rec = {"ms_per_year": ms_fwd, "model_years_per_s": 1000.0 / ms_fwd,
            "cost_vs_headline": ms_fwd / ms_plain, "adjoint_ms": ms_adj, "adjoint_forward_ratio": ms_adj / ms_fwd,
-           "forward_path": "k_year_bins" if t.query(tmm.TMM_Q_PERSISTENT) else "k_step_stream",
-           "adjoint_path": "k_adjoint_bins" if t.query(tmm.TMM_Q_PERSISTENT_ADJOINT) else "k_adjoint",
+           "forward_path": year_kernel(t), "adjoint_path": adjoint_kernel(t),
            "adjoint_ckpt_every": inp.nstep}
     log(f"[bench] {label}: {ms_fwd:.3f} ms/model-year ({ms_fwd / ms_plain:.2f}x), "
         f"adjoint {ms_adj:.2f} ms (ratio {ms_adj / ms_fwd:.2f}, {rec['adjoint_path']})")
     t.close()
     return rec
+
+
+def year_kernel(t):
+    """The kernel a handle's one-member model years run, in the library's default options."""
+    from paper_1410_0204_amd import tmm
+    if t.query(tmm.TMM_Q_PERSISTENT):
+        return "k_year_bins" if t.query(tmm.TMM_Q_BIN_LANES) else "k_year_persistent"
+    return "k_step_stream" if int(t.desc.nlayer) <= 24 and int(t.desc.nbgc) <= 1 else "k_step"
+
+
+def adjoint_kernel(t):
+    """The kernel a handle's one-member reverse sweeps run."""
+    from paper_1410_0204_amd import tmm
+    if t.query(tmm.TMM_Q_PERSISTENT_ADJOINT):
+        return "k_adjoint_bins" if t.query(tmm.TMM_Q_BIN_LANES) else "k_adjoint_persistent"
+    return "k_adjoint"
 
 
 def _events():
@@ -653,8 +668,8 @@ def bench_grids(args):
         t.close()
         del t
         torch.cuda.empty_cache()
-    print(json.dumps({"mode": "grids", "kernel": "k_step_stream (graph-replayed, one launch per step)", "rows": rows}),
-          flush=True)
+    print(json.dumps({"mode": "grids", "kernel": {"default": "k_step_stream", "tile_rows_*": "k_step"},
+                      "launch": "graph-replayed, one launch per step", "rows": rows}), flush=True)
 
 
 def bench_newton(args):

@@ -264,8 +264,12 @@ enum {
                                 at most 8 latitude rows per domain, and the table fits beside the halo
                                 with every domain resident); 0 if it loads it every step.  The tangent
                                 kernel decides the same on its own, larger LDS */
-    TMM_Q_WAVE_LOCAL = 7     /* 1 if the persistent forward kernels run with wave-aligned water
+    TMM_Q_WAVE_LOCAL = 7,    /* 1 if the persistent forward kernels run with wave-aligned water
                                 columns (option TMM_OPT_WAVE_LOCAL) */
+    TMM_Q_BIN_LANES = 8      /* lanes of the bins that hold the water columns of the persistent kernels:
+                                16 or 32 (k_year_bins, k_adjoint_bins); 0 where the persistent
+                                kernels of the other layout run (k_year_persistent,
+                                k_adjoint_persistent), or none */
 };
 
 /* Sets an execution option; results are the same either way up to rounding

@@ -2286,6 +2286,7 @@ int tmm_query(tmm_handle h, int what, long long* value) {
             return TMM_OK;
         case TMM_Q_INSOLATION_LDS: *value = (h->pers_ok && h->pers_ql[0]) ? 1 : 0; return TMM_OK;
         case TMM_Q_WAVE_LOCAL: *value = (h->pers_ok && h->pers_wave_local) ? 1 : 0; return TMM_OK;
+        case TMM_Q_BIN_LANES: *value = h->pers_ok ? 16 * h->bins : 0; return TMM_OK;
         default: return TMM_EINVAL;
     }
 }

@@ -50,6 +50,7 @@ TMM_Q_COMPUTE_UNITS = 4
 TMM_Q_PERSISTENT_ADJOINT = 5
 TMM_Q_INSOLATION_LDS = 6
 TMM_Q_WAVE_LOCAL = 7
+TMM_Q_BIN_LANES = 8
 
 EXPORTED = (
     "tmm_workspace_bytes", "tmm_create", "tmm_destroy", "tmm_set_params", "tmm_step", "tmm_year",
