@@ -232,7 +232,9 @@ enum {
                                     the domains allow it (more, smaller domains if needed), so that
                                     a time step needs one workgroup barrier instead of three; 0:
                                     packed columns and three barriers per step.  Rebuilds the
-                                    domains; the forward results are the same bit for bit */
+                                    domains.  With one or two tracers and one BGC evaluation per
+                                    step the forward results are the same bit for bit, else up to
+                                    rounding */
     TMM_OPT_MEMBER_TILE = 11,    /* 0 (default): member-parallel steps of two-tracer models use one
                                     wavefront per water column that reads its stencil's state rows
                                     itself; 4 or 8: workgroups of that many neighbouring columns
