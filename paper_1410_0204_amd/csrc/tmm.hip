@@ -376,19 +376,18 @@ struct tmm_ctx {
     std::vector<double> h_vec;
     // persistent year kernel
     bool pers_ok = false;          // tables built and the launch fits the device
-    bool pers_adj_ok = false;      // ... and so does the persistent adjoint
     bool pers_enabled = true;      // option TMM_OPT_PERSISTENT
     long long spin_limit = 1ll << 22;   // option TMM_OPT_SPIN_LIMIT
     int pers_G = 0;
-    int pers_M = 1;                // members one launch runs side by side
+    int pers_M = 1;                // members one launch runs side by side,
+    int pers_Madj = 0;             // ... one launch of the reverse sweep (0: it does not fit),
+    int pers_qlM[2] = {0, 0};      // ... one with the insolation table in LDS [tangent] (0: none)
     int bins = 0;                  // 16-lane rows per bin of the binned layout (0: the layout of tmm_persistent.hpp)
     int pers_kmax = 16;
     int pers_tpb = 256;            // threads (= maximum rows) per domain
     int pers_hmax = 0;             // largest domain halo (rows)
     int pers_ahmax = 0;            // ... of the transposed stencil
     int pers_qmax = 0;             // most latitude rows a domain spans (its insolation table in LDS)
-    bool pers_ql[2] = {false, false};   // the forward kernels keep that table in LDS (state
-                                        // only, with the tangent)
     bool pers_wave_local = false;  // no water column spans two wavefronts of the forward kernels
     bool wave_local_enabled = true;    // option TMM_OPT_WAVE_LOCAL
     int pers_target = 0;           // option TMM_OPT_DOMAIN_ROWS as last set
@@ -966,7 +965,7 @@ int launch_persistent(tmm_ctx* h, int M, int slot0, tmm::StepRange sr, tmm::Stat
     tmm::Persist ps = persist_args(h);
     double dtd = tmm::kDaysPerYear / P.nstep;
     const bool tangent = v.p != nullptr;
-    const bool ql = h->pers_ql[tangent ? 1 : 0];
+    const bool ql = M <= h->pers_qlM[tangent ? 1 : 0];
     if (h->bins) {
         tmm::Bins bn = bins_args(h, tangent, false);
         void* args[] = {&g, &md, &mt, &ps, &bn, &sr, &dtd, &slot0, &y, &out, &v, &vout};
@@ -1439,10 +1438,10 @@ int build_bins(tmm_ctx* h, int target_rows, int ncu) {
     h->pers_hmax = hmax;
     h->pers_ahmax = ahmax;
     h->pers_qmax = std::max(qrows, 0);
-    h->pers_ql[0] = h->pers_ql[1] = ql;
+    h->pers_Madj = adj_ok ? h->pers_M : 0;
+    h->pers_qlM[0] = h->pers_qlM[1] = ql ? h->pers_M : 0;
     h->pers_wave_local = true;
     h->pers_ok = true;
-    h->pers_adj_ok = adj_ok;
     return TMM_OK;
 }
 
@@ -1459,7 +1458,7 @@ int build_persistent(tmm_ctx* h, int target_rows) {
     TMM_TRY(hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev));
     h->num_cu = ncu;
     h->pers_ok = false;
-    h->pers_adj_ok = false;
+    h->pers_Madj = 0;
     h->pers_target = target_rows;
     h->bins = 0;
     if (!coop || !P.o_ring || P.ew > tmm::kEllMax || P.nlayer > 32 || P.neu > tmm::kNeuMax) return TMM_OK;
@@ -1582,23 +1581,21 @@ int build_persistent(tmm_ctx* h, int target_rows) {
     const bool ql = sn == 0 && qmax > 0;
     qmax = std::max(qmax, 0);
     // decided per mode: the tangent's larger LDS may not leave room for the
-    // table (or for the co-residency of all domains) where the state's does
-    bool ql_mode[2] = {ql, ql};
+    // table (or for the co-residency of all domains) where the state's does;
+    // and per launch: fewer members may fit side by side with it than without
+    int ql_members[2] = {0, 0};
     for (int t = 0; t < 2 && ql; ++t) {
         const void* fk = persistent_kernel(P.ntr, t, h->pers_kmax, tpb, sn, true);
         const size_t dyn = tmm::year_kernel_dyn_lds(tpb, hmax, P.ntr, t, qmax, P.nstep);
         hipFuncAttributes attr;
         TMM_TRY(hipFuncGetAttributes(&attr, fk));
-        if (attr.sharedSizeBytes + dyn > (size_t)lds_max) {
-            ql_mode[t] = false;
-            continue;
-        }
+        if (attr.sharedSizeBytes + dyn > (size_t)lds_max) continue;
         TMM_TRY(ensure_dyn_lds(fk, dyn));
         int o = 0;
         TMM_TRY(hipOccupancyMaxActiveBlocksPerMultiprocessor(&o, fk, tpb, dyn));
-        if ((long long)ncu * o < (long long)std::max(1, std::min(P.pers_members, maxG / G)) * G) ql_mode[t] = false;
+        ql_members[t] = ncu * o / G;
     }
-    if (!ql_mode[0] && !ql_mode[1]) qmax = 0;
+    if (!ql_members[0] && !ql_members[1]) qmax = 0;
     const std::vector<int> block_dom = xcd_order(G);
     if (upload(h, h->at<int>(P.o_pblock), block_dom.data(), (size_t)G * 4) ||
         upload(h, h->at<int>(P.o_pdomcol), dom.data(), dom.size() * 4) ||
@@ -1620,11 +1617,11 @@ int build_persistent(tmm_ctx* h, int target_rows) {
     h->pers_hmax = hmax;
     h->pers_ahmax = ahmax;
     h->pers_qmax = qmax;
-    h->pers_ql[0] = ql_mode[0];
-    h->pers_ql[1] = ql_mode[1];
+    h->pers_Madj = ahalo_ok ? std::min(h->pers_M, ncu * occ_adj / G) : 0;
+    h->pers_qlM[0] = ql_members[0];
+    h->pers_qlM[1] = ql_members[1];
     h->pers_wave_local = wave_local;
     h->pers_ok = true;
-    h->pers_adj_ok = ahalo_ok && (long long)ncu * occ_adj >= (long long)h->pers_M * G;
     return TMM_OK;
 }
 
@@ -1648,7 +1645,7 @@ int sqdiff(tmm_ctx* h, int nb, const double* a, const double* b, int volume, dou
 
 
 // Checkpointed adjoint of one model year with persistent launches, for nb
-// members, pers_M at a time: a forward sweep storing y every ckpt steps and
+// members, as many at a time as the sweep at hand fits side by side: a forward sweep storing y every ckpt steps and
 // the month-end misfit sums; the misfit source of the last month and Ai^T for
 // the last step; then per segment, last first, a forward replay storing every
 // state and a reverse sweep over the segment.  The forward sweep writes the
@@ -1713,8 +1710,8 @@ int adjoint_persistent(tmm_ctx* h, int nb, const double* y0, const double* obs, 
                                nullptr);
         TMM_LAUNCHED();
     }
-    for (int s = 0; s < nb; s += h->pers_M) {
-        const int M = std::min(h->pers_M, nb - s);
+    for (int s = 0; s < nb; s += h->pers_Madj) {
+        const int M = std::min(h->pers_Madj, nb - s);
         const tmm::StateView ob = batch_view(h, obs, W, s);
         double* sg_store = seg + (size_t)s * seg_step;
         int im = 0;
@@ -2282,9 +2279,9 @@ int tmm_query(tmm_handle h, int what, long long* value) {
         case TMM_Q_WORKSPACE: *value = (long long)h->P.total; return TMM_OK;
         case TMM_Q_COMPUTE_UNITS: *value = h->num_cu; return TMM_OK;
         case TMM_Q_PERSISTENT_ADJOINT:
-            *value = (h->pers_ok && h->pers_adj_ok && h->P.etw <= tmm::kEllMax) ? 1 : 0;
+            *value = (h->pers_ok && h->pers_Madj > 0 && h->P.etw <= tmm::kEllMax) ? 1 : 0;
             return TMM_OK;
-        case TMM_Q_INSOLATION_LDS: *value = (h->pers_ok && h->pers_ql[0]) ? 1 : 0; return TMM_OK;
+        case TMM_Q_INSOLATION_LDS: *value = (h->pers_ok && h->pers_qlM[0] > 0) ? 1 : 0; return TMM_OK;
         case TMM_Q_WAVE_LOCAL: *value = (h->pers_ok && h->pers_wave_local) ? 1 : 0; return TMM_OK;
         case TMM_Q_BIN_LANES: *value = h->pers_ok ? 16 * h->bins : 0; return TMM_OK;
         default: return TMM_EINVAL;
@@ -2423,7 +2420,7 @@ int tmm_year_adjoint(tmm_handle h, const double* y0, const double* obs, int ckpt
     const size_t n = P.n, len = n * W;
     const int K = P.ckpt, spm = P.nstep / P.nmat, nseg = P.nstep / K;
     const double dtd = tmm::kDaysPerYear / P.nstep;
-    if (h->pers_adj_ok && P.etw <= tmm::kEllMax && single_launch(h, nb, true))
+    if (h->pers_Madj > 0 && P.etw <= tmm::kEllMax && single_launch(h, nb, true))
         return adjoint_persistent(h, nb, y0, obs, J_host, dJdu_host, dJdy0);
     const Tiling& tl = h->tiling_for(W, 1, 256 * 8 * np);
     tmm::Grid g = h->grid(tl);

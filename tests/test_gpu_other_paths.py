@@ -160,3 +160,41 @@ def test_launch_per_step_batches(model, nbgc, nlayer):
     t.set_option(tmm.TMM_OPT_PERSISTENT, 0)
     t.set_option(tmm.TMM_OPT_MEMBER_KERNEL_MIN, 0)
     _check(t, inp, oracle.Oracle(inp), label)
+
+
+@pytest.mark.parametrize("rows", [64, 128])
+@pytest.mark.parametrize("model", [N, NDOP, PHY])
+def test_a_batch_handle_keeps_what_one_member_has(model, rows):
+    """A handle for several members offers one member's years and gradients the same kernels as a handle
+    for one: how many members fit the device side by side decides how many run in a launch, not whether
+    the reverse sweep is one launch or the insolation stands in LDS."""
+    import torch
+    tmm = _tmm()
+    for nstep in (2880, NSTEP):            # (the table holds the year's steps)
+        inp = synth.custom(60, 48, 10, 1900, 14000, model=model, nstep=nstep)
+        got = []
+        for nb in (1, 4):
+            print(f"[gpu] batch handle model={model} rows={rows} nstep={nstep} members={nb}", flush=True)
+            t = tmm.TMM(inp.desc_arrays(), nbatch_max=nb, adjoint_nbatch_max=nb, ckpt_every=48)
+            t.set_option(tmm.TMM_OPT_WAVE_LOCAL, 0)
+            t.set_option(tmm.TMM_OPT_DOMAIN_ROWS, rows)
+            got.append([t.query(q) for q in (tmm.TMM_Q_PERSISTENT, tmm.TMM_Q_DOMAINS, tmm.TMM_Q_PERSISTENT_ADJOINT,
+                                             tmm.TMM_Q_INSOLATION_LDS)])
+        print(f"[gpu] one member, batch: {got}", flush=True)
+        assert got[0] == got[1]
+    # and the batch's years and gradients, members side by side, give each member's own
+    ntr, nb = inp.ntracer, 4
+    u = _params(inp, nb)
+    rng = np.random.default_rng(6)
+    y = inp.initial_state(nb).reshape(inp.n, nb * ntr) * rng.uniform(0.8, 1.2, size=(inp.n, nb * ntr))
+    obs = np.broadcast_to(y, (inp.nmat,) + y.shape) * rng.uniform(0.9, 1.1, size=(inp.nmat,) + y.shape)
+    t.set_params(u)
+    years = t.year(t.state(y))[0].cpu().numpy()
+    J, G, dy0 = t.year_adjoint(t.state(y), torch.as_tensor(np.ascontiguousarray(obs)).cuda())
+    dy0, G, o = dy0.cpu().numpy(), np.asarray(G).reshape(nb, -1), oracle.Oracle(inp)
+    for b in (0, nb - 1):
+        assert pointwise(_col(years, b, ntr), o.year(u[b], _col(y, b, ntr))[0], ntr, f"member {b}") <= YEAR
+        eJ, eG, eY = o.year_adjoint(u[b], _col(y, b, ntr), _col(obs, b, ntr))
+        assert componentwise(np.ravel(J)[b], eJ, "J") <= MISFIT
+        assert componentwise(G[b], eG, f"dJ/du {b}") <= ADJOINT
+        assert columnwise(_col(dy0, b, ntr), eY, ntr, f"dJ/dy0 {b}") <= ADJOINT
