@@ -893,27 +893,11 @@ const void* bins_adjoint_kernel(const tmm_ctx* h) {
                          : tmm::bins_adjoint_kernel_1(sub, h->bins);
 }
 
-// Pause before the first poll of a step (64-cycle units, see hold_poll), the
-// measured optimum of the three kernels by the work a step does before it:
-// none where internal BGC steps already take longer than a value needs to
-// arrive; less in 32-lane bins (twice the product) and on few domains (a store
-// is seen sooner).  Model year on the 128x64x15 grid, ms at 0 / 5 / 7 / 9 / 12:
-// PO4-DOP 4.35 / 3.85 / 3.64 / 3.73 / 3.92, PO4-DOP-PHY 6.30 / 5.62 / 5.28 /
-// 5.10 / 5.18; its tangent year 6.02 / 5.60 / 5.53 / 5.56 / 5.67; on the
-// 32x16x8 grid (12 domains) 3.22 at 0, 3.08 at 2, 3.32 at 7.
-int poll_hold(const tmm_ctx* h, bool tangent, bool reverse) {
-    if (h->P.nsub > 1) return 0;
-    const bool few = h->pers_G * h->pers_M < 64;
-    if (reverse) return few ? 1 : (h->bins == 2 ? 2 : 6);
-    if (tangent) return few ? 0 : (h->bins == 2 ? 2 : 6);
-    const int base = h->P.ntr == 3 ? 9 : 7;
-    return few ? 3 : (h->bins == 2 ? base - 3 : base);
-}
-
-tmm::Bins bins_args(const tmm_ctx* h, bool tangent, bool reverse) {
+// Arguments of a launch of M members.
+tmm::Bins bins_args(const tmm_ctx* h, int M, bool tangent, bool reverse) {
     const Plan& P = h->P;
     tmm::Bins b;
-    b.hold = poll_hold(h, tangent, reverse);
+    b.hold = tmm::poll_pause(P.nsub > 1, 16 * h->bins, P.ntr, h->pers_G * M, tangent, reverse);
     b.lane = h->at<int4>(P.o_blane);
     b.ae_lds = h->at<int>(P.o_bae);
     b.aet_lds = h->at<int>(P.o_baet);
@@ -967,7 +951,7 @@ int launch_persistent(tmm_ctx* h, int M, int slot0, tmm::StepRange sr, tmm::Stat
     const bool tangent = v.p != nullptr;
     const bool ql = M <= h->pers_qlM[tangent ? 1 : 0];
     if (h->bins) {
-        tmm::Bins bn = bins_args(h, tangent, false);
+        tmm::Bins bn = bins_args(h, M, tangent, false);
         void* args[] = {&g, &md, &mt, &ps, &bn, &sr, &dtd, &slot0, &y, &out, &v, &vout};
         TMM_TRY(hipLaunchCooperativeKernel(bins_year_kernel(h, tangent, ql), dim3(h->pers_G, M),
                                            dim3(tmm::kBinThreads), args,
@@ -1013,7 +997,7 @@ int launch_adjoint_persistent(tmm_ctx* h, int M, int slot0, int j_lo, int j_hi, 
     tmm::Persist ps = persist_args(h);
     double dtd = tmm::kDaysPerYear / P.nstep;
     if (h->bins) {
-        tmm::Bins bn = bins_args(h, false, true);
+        tmm::Bins bn = bins_args(h, M, false, true);
         void* args[] = {&g, &md, &mt, &ps, &bn, &dtd, &slot0, &j_lo, &j_hi, &ystore, &ystore_step, &obs, &obs_month,
                         &src_scale, &mu_in, &mu_out, &ubar_dom, &ubar_ld};
         TMM_TRY(hipLaunchCooperativeKernel(bins_adjoint_kernel(h), dim3(h->pers_G, M), dim3(tmm::kBinThreads), args,

@@ -13,4 +13,23 @@ constexpr int kBinThreads = 256;       // lanes per workgroup of the binned kern
 constexpr int bins_cells(int halo_max) { return kBinThreads + (halo_max + 1) / 2 * 2; }
 constexpr int bins_buffer_bytes(int halo_max, int ntr) { return bins_cells(halo_max) * ntr * 8; }
 
+// Pause before the first poll of a step (64-cycle units, see hold_poll), the
+// measured optimum of the three kernels by the work a step does before it:
+// none where internal BGC steps already take longer than a value needs to
+// arrive; less in 32-lane bins (twice the product) and in launches of few
+// workgroups (a store is seen sooner).  lanes: 16 or 32 per bin; workgroups:
+// the launch's, over all its members.  Model year on the 128x64x15 grid, ms at
+// 0 / 5 / 7 / 9 / 12: PO4-DOP 4.35 / 3.85 / 3.64 / 3.73 / 3.92, PO4-DOP-PHY
+// 6.30 / 5.62 / 5.28 / 5.10 / 5.18; its tangent year 6.02 / 5.60 / 5.53 / 5.56
+// / 5.67; on the 32x16x8 grid (12 domains) 3.22 at 0, 3.08 at 2, 3.32 at 7.
+constexpr int kFewWorkgroups = 64;
+constexpr int poll_pause(bool internal_steps, int lanes, int ntr, int workgroups, bool tangent, bool reverse) {
+    if (internal_steps) return 0;
+    const bool few = workgroups < kFewWorkgroups;
+    if (reverse) return few ? 1 : (lanes == 32 ? 2 : 6);
+    if (tangent) return few ? 0 : (lanes == 32 ? 2 : 6);
+    const int base = ntr == 3 ? 9 : 7;
+    return few ? 3 : (lanes == 32 ? base - 3 : base);
+}
+
 }  // namespace tmm

@@ -13,6 +13,9 @@ SHIM = r"""
 extern "C" {
 int bins_cells(int halo_max) { return tmm::bins_cells(halo_max); }
 int bins_buffer_bytes(int halo_max, int ntr) { return tmm::bins_buffer_bytes(halo_max, ntr); }
+int poll_pause(int sub, int lanes, int ntr, int workgroups, int tangent, int reverse) {
+    return tmm::poll_pause(sub, lanes, ntr, workgroups, tangent, reverse);
+}
 }
 """
 
@@ -35,3 +38,15 @@ def test_binned_lds_buffers_start_on_16_bytes(rules, ntr):
         assert rules.bins_cells(halo) >= 256 + halo
         assert rules.bins_buffer_bytes(halo, ntr) == rules.bins_cells(halo) * ntr * 8
         assert rules.bins_buffer_bytes(halo, ntr) % 16 == 0, halo
+
+
+def test_poll_pause_goes_by_the_launch(rules):
+    """A launch of few workgroups (one member of a 12-domain grid) pauses briefly before its first poll,
+    whatever number of members its handle could hold; one of many (21 members of that grid) longer."""
+    assert [rules.poll_pause(0, 16, 2, g, 0, 0) for g in (1, 12, 63, 64, 252)] == [3, 3, 3, 7, 7]
+    assert [rules.poll_pause(0, 16, 3, g, 0, 0) for g in (12, 252)] == [3, 9]
+    assert [rules.poll_pause(0, 32, 2, g, 0, 0) for g in (12, 252)] == [3, 4]
+    assert [rules.poll_pause(0, lanes, 2, 252, 1, 0) for lanes in (16, 32)] == [6, 2]
+    assert [rules.poll_pause(0, lanes, 2, 252, 0, 1) for lanes in (16, 32)] == [6, 2]
+    assert [rules.poll_pause(0, 16, 2, 12, t, r) for t, r in ((1, 0), (0, 1))] == [0, 1]
+    assert all(rules.poll_pause(1, 16, 2, g, t, r) == 0 for g in (12, 252) for t in (0, 1) for r in (0, 1))
