@@ -1346,8 +1346,8 @@ int build_bins(tmm_ctx* h, int target_rows, int ncu) {
         }
     std::vector<int> dep_ptr, dep_idx, halo_ptr, halo, ahalo_ptr, ahalo, qlat;
     domain_deps(h, row_dom, G, dep_ptr, dep_idx);
-    const int hmax = domain_halos(h, row_dom, row_cell, G, false, halo_ptr, halo);
-    const int ahmax = domain_halos(h, row_dom, row_cell, G, true, ahalo_ptr, ahalo);
+    const int hmax = tmm::bins_halo(domain_halos(h, row_dom, row_cell, G, false, halo_ptr, halo));
+    const int ahmax = tmm::bins_halo(domain_halos(h, row_dom, row_cell, G, true, ahalo_ptr, ahalo));
     const int halo_cap = tmm::kHaloPerThread * TPB;
     if (hmax > halo_cap || ahmax > halo_cap || dep_idx.size() > P.dep_capacity || halo.size() > P.halo_capacity ||
         ahalo.size() > P.halo_capacity)

@@ -64,7 +64,7 @@ struct Bins {
     const int* halo_cell;   // ring cells of other domains each domain reads, ascending per domain
     const int* ahalo_ptr;
     const int* ahalo_cell;
-    int halo_max, ahalo_max;
+    int halo_max, ahalo_max; // largest halos, rounded up by bins_halo()
     int cells;              // ring cells of a slot (rows, padded to a multiple of 64)
     int hold;               // pause before a step's first poll, in units of 64 cycles (see hold_poll)
 };
@@ -72,12 +72,12 @@ struct Bins {
 // Dynamic LDS of the forward kernel: two buffers of own lanes and halo for y
 // (and v).
 __host__ __device__ inline size_t bins_year_lds(int halo_max, int ntr, bool tangent) {
-    return (size_t)bins_buffer_bytes(halo_max, ntr) * 2 * (tangent ? 2 : 1);
+    return (size_t)(kBinThreads + halo_max) * ntr * 8 * 2 * (tangent ? 2 : 1);
 }
 // ... and of the reverse sweep: two buffers of mu, then the internal-step
 // states [nsub][kBinThreads][ntr] (nsub = 0: none).
 __host__ __device__ inline size_t bins_adjoint_lds(int ahalo_max, int ntr, int nsub) {
-    return (size_t)bins_buffer_bytes(ahalo_max, ntr) * 2 + (size_t)nsub * kBinThreads * ntr * 8;
+    return (size_t)(kBinThreads + ahalo_max) * ntr * 8 * 2 + (size_t)nsub * kBinThreads * ntr * 8;
 }
 
 typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
@@ -453,8 +453,8 @@ __global__ __launch_bounds__(kBinThreads, 1) void k_year_bins(Grid g, Model md, 
     __shared__ double s_red[TPB];
     __shared__ double s_ins[QL ? 2 * kInsLat * kRingK : 1];
     extern __shared__ __align__(16) char s_bytes[];
-    const int len = bins_cells(bn.halo_max);      // cells of a buffer
-    const int buf = bins_buffer_bytes(bn.halo_max, NTR);   // its bytes; y of state jj in buffer jj % 2, then v's two
+    const int len = TPB + bn.halo_max;            // cells of a buffer
+    const int buf = len * NTR * 8;                // its bytes; y of state jj in buffer jj % 2, then v's two
 
     const int tid = threadIdx.x;
     const int ms = blockIdx.y;
@@ -775,8 +775,8 @@ __global__ __launch_bounds__(kBinThreads, 1) void k_adjoint_bins(Grid g, Model m
     __shared__ int s_fail;
     __shared__ double s_red[TPB];
     extern __shared__ __align__(16) char s_bytes[];
-    const int len = bins_cells(bn.ahalo_max);
-    const int buf = bins_buffer_bytes(bn.ahalo_max, NTR);
+    const int len = TPB + bn.ahalo_max;
+    const int buf = len * NTR * 8;
     double* const s_traj = reinterpret_cast<double*>(s_bytes + 2 * buf);
 
     const int tid = threadIdx.x;

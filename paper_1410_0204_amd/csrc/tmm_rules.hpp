@@ -6,12 +6,14 @@ namespace tmm {
 
 constexpr int kBinThreads = 256;       // lanes per workgroup of the binned kernels
 
-// Cells of one LDS buffer of the binned kernels: the own lanes, then the halo.
-// An even number, so that the second buffer starts on 16 bytes with three
-// tracers (24 bytes a cell) as well: its cells are read and written as
-// 16-byte vectors.
-constexpr int bins_cells(int halo_max) { return kBinThreads + (halo_max + 1) / 2 * 2; }
-constexpr int bins_buffer_bytes(int halo_max, int ntr) { return bins_cells(halo_max) * ntr * 8; }
+// Halo cells of an LDS buffer of the binned kernels (which holds the own lanes,
+// then the halo) for a largest halo of that many rows: an even number, so that
+// the second buffer starts on 16 bytes with three tracers (24 bytes a cell) as
+// well: its cells are read and written as 16-byte vectors.  Rounded here and
+// not in the kernels: told that the length is even, the compiler spilled a
+// register of k_adjoint_bins<3, true, .> to an accumulation register ahead of
+// the restoring of exec, where only some lanes store it.
+constexpr int bins_halo(int rows) { return (rows + 1) / 2 * 2; }
 
 // Pause before the first poll of a step (64-cycle units, see hold_poll), the
 // measured optimum of the three kernels by the work a step does before it:

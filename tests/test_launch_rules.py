@@ -11,8 +11,7 @@ CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))),
 SHIM = r"""
 #include "tmm_rules.hpp"
 extern "C" {
-int bins_cells(int halo_max) { return tmm::bins_cells(halo_max); }
-int bins_buffer_bytes(int halo_max, int ntr) { return tmm::bins_buffer_bytes(halo_max, ntr); }
+int bins_halo(int rows) { return tmm::bins_halo(rows); }
 int poll_pause(int sub, int lanes, int ntr, int workgroups, int tangent, int reverse) {
     return tmm::poll_pause(sub, lanes, ntr, workgroups, tangent, reverse);
 }
@@ -35,9 +34,8 @@ def test_binned_lds_buffers_start_on_16_bytes(rules, ntr):
     """The binned kernels keep two buffers one after the other in LDS and access their cells as 16-byte
     vectors: whatever the halo of a grid's domains, a buffer holds it and ends on 16 bytes."""
     for halo in range(0, 513):
-        assert rules.bins_cells(halo) >= 256 + halo
-        assert rules.bins_buffer_bytes(halo, ntr) == rules.bins_cells(halo) * ntr * 8
-        assert rules.bins_buffer_bytes(halo, ntr) % 16 == 0, halo
+        assert halo <= rules.bins_halo(halo) <= 512
+        assert (256 + rules.bins_halo(halo)) * ntr * 8 % 16 == 0, halo
 
 
 def test_poll_pause_goes_by_the_launch(rules):
