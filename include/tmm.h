@@ -112,13 +112,20 @@ typedef struct {
 } tmm_desc;
 
 /* Device workspace size for a descriptor.  Returns TMM_EINVAL for a bad
- * descriptor. */
+ * descriptor.
+ * Its largest part on small grids are the rings of the single-launch year
+ * kernels, 128 states (n rounded up to a multiple of 64) each, two for every
+ * member that may run side by side: min(nbatch_max, 256, 65536 / n) members
+ * (one where n > 65536), none where the kernels cannot run (more than 32
+ * layers, 4 euphotic layers, 8 explicit entries per row or 131072 points). */
 int tmm_workspace_bytes(const tmm_desc *desc, size_t *bytes);
 
 /* Validates the descriptor, converts the matrices to the device formats and
- * uploads them into the workspace (device pointer, at least
- * tmm_workspace_bytes() bytes, 256-byte aligned).  hip_stream is a
- * hipStream_t (NULL = default stream) used by every later call. */
+ * uploads them into the workspace (device pointer, tmm_workspace_bytes()
+ * bytes, 256-byte aligned).  hip_stream is a hipStream_t (NULL = default
+ * stream) used by every later call.  A workspace that is smaller by whole
+ * rings, down to two of them, is accepted: fewer members of a batch then run
+ * side by side, with the same results.  TMM_ENOMEM below that. */
 int tmm_create(const tmm_desc *desc, void *dev_workspace, size_t bytes,
                void *hip_stream, tmm_handle *out);
 

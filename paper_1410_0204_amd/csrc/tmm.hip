@@ -135,8 +135,10 @@ struct Plan {
     size_t o_pblock, o_pdomcol, o_pdepptr, o_pdepidx, o_pflags, o_pabort;
     size_t o_finite;                // set by the per-year non-finite check
     size_t o_probe;                 // words, results and load chain of tmm_probe_exchange
-    size_t o_ring, o_vring;         // state rings of the persistent forward kernel (0: none)
-    int pers_members;               // members they hold
+    bool pers_possible;             // layers, stencil and size the single-launch kernels take
+    size_t o_ring, ring_bytes;      // state rings of the persistent kernels (0: none), at the workspace's end:
+    int rings;                      // one per member of a launch, two where the tangent goes along
+    int side_by_side;               // members of a launch at most
     size_t o_phaloptr, o_phalo;     // halo rows of each domain
     size_t o_pqlat;                 // latitude rows of each domain (insolation table in LDS)
     size_t o_pcolslot;              // first slot (thread) of each water column in its domain
@@ -148,11 +150,12 @@ struct Plan {
 };
 
 constexpr int kMaxDomains = 4096;
-constexpr int kMaxBinDomains = 1024;        // domains of the binned layout (one per compute unit at most)
+constexpr int kMaxBinDomains = 256;         // domains of the binned layout (one per compute unit at most)
 // grids up to this many rows get the persistent kernel's state rings
 // (2 x kRing x n x ntr doubles); larger ones cannot be resident anyway
 constexpr int kMaxPersistentRows = 256 * tmm::kPersistThreadsMax;
-constexpr int kMemberRingRows = 65536;      // rows over all members of one launch (sizes the rings)
+constexpr int kMemberRingRows = 65536;      // rows over all members of one launch,
+constexpr int kMemberRings = 256;           // ... and members: what the compute units can hold (256 rows each)
 constexpr int kDefaultDomainRows = 256;     // rows per persistent workgroup unless set by option (tuned on MI355X)
 constexpr int kMembersWavesMax = 8;         // wavefronts per workgroup of the member kernel, at most
 constexpr int kDefaultBandRows = 16;        // latitude rows per band of the member kernel's column order
@@ -277,6 +280,10 @@ int validate(const tmm_desc* d, Plan& P) {
         P.o_stile = take((size_t)make_tiles(P.col_start, tmm::kStreamRows).size() * 16);
         P.o_srow = take(npad * 8);
     }
+    // the single-launch kernels' limits; a domain holds at least one water column
+    P.pers_possible = d->n <= kMaxPersistentRows && P.ew <= tmm::kEllMax && d->nlayer <= 32 && P.neu <= tmm::kNeuMax;
+    P.bins_possible = P.pers_possible && P.ew <= tmm::kBinEll && P.etw <= tmm::kBinEll;
+    const size_t most_domains = P.pers_possible ? std::min(kMaxDomains, d->ncol) : 0;
     const size_t nbm = d->nbatch_max;
     P.o_u = take(nbm * P.nparam * 8);
     P.o_light = take(nbm * d->nlayer * 8);
@@ -304,8 +311,8 @@ int validate(const tmm_desc* d, Plan& P) {
         P.o_final = take(astate);
         P.o_mu[0] = take(astate);
         P.o_mu[1] = take(astate);
-        P.o_pubar = take((size_t)kMaxDomains * P.adj_nb * P.nparam * 8);
-        P.o_pjpart = take(nm * kMaxDomains * P.adj_nb * 8);
+        P.o_pubar = take(most_domains * P.adj_nb * P.nparam * 8);
+        P.o_pjpart = take(nm * most_domains * P.adj_nb * 8);
     } else {
         P.o_pubar = P.o_pjpart = 0;
         P.o_ubt = P.o_jpart = P.o_ckpt = P.o_seg = P.o_final = P.o_mu[0] = P.o_mu[1] = 0;
@@ -340,23 +347,23 @@ int validate(const tmm_desc* d, Plan& P) {
     P.o_pahalo = take(P.halo_capacity * 4);
     P.o_pqlat = take((size_t)kMaxDomains * (1 + tmm::kInsLat) * 4);
     P.o_pcolslot = take((size_t)d->ncol * 4);
-    P.bins_possible = d->n <= kMaxPersistentRows && P.ew <= tmm::kBinEll && P.etw <= tmm::kBinEll && d->nlayer <= 32;
-    if (d->n <= kMaxPersistentRows) {
-        P.o_blane = take((size_t)kMaxBinDomains * tmm::kBinThreads * 16);
+    if (P.pers_possible) {
+        P.o_blane = take((size_t)std::min(kMaxBinDomains, d->ncol) * tmm::kBinThreads * 16);
         P.o_bae = take((size_t)tmm::kBinEll * npad * 4);
         P.o_baet = take((size_t)tmm::kBinEll * npad * 4);
         P.o_bcell = take(npad * 4);
     } else {
         P.o_blane = P.o_bae = P.o_baet = P.o_bcell = 0;
     }
-    if (d->n <= kMaxPersistentRows) {
-        // rings for the members that one launch may run side by side
-        P.pers_members = std::min(d->nbatch_max, std::max(1, kMemberRingRows / d->n));
-        P.o_ring = take((size_t)P.pers_members * tmm::kRing * npad * P.ntr * 8);
-        P.o_vring = take((size_t)P.pers_members * tmm::kRing * npad * P.ntr * 8);
-    } else {
-        P.pers_members = 0;
-        P.o_ring = P.o_vring = 0;
+    // rings for the members that one launch may run side by side, and their
+    // tangents; last, so that a workspace that holds fewer of them serves too
+    P.o_ring = P.ring_bytes = 0;
+    P.rings = 0;
+    P.side_by_side = std::min(d->nbatch_max, std::max(1, std::min(kMemberRings, kMemberRingRows / d->n)));
+    if (P.pers_possible) {
+        P.rings = 2 * P.side_by_side;
+        P.ring_bytes = (size_t)tmm::kRing * npad * P.ntr * 8;
+        P.o_ring = take(P.rings * P.ring_bytes);
     }
     P.total = o;
     return TMM_OK;
@@ -379,7 +386,7 @@ struct tmm_ctx {
     bool pers_enabled = true;      // option TMM_OPT_PERSISTENT
     long long spin_limit = 1ll << 22;   // option TMM_OPT_SPIN_LIMIT
     int pers_G = 0;
-    int pers_M = 1;                // members one launch runs side by side,
+    int pers_M[2] = {1, 1};        // members one launch runs side by side [with their tangents],
     int pers_Madj = 0;             // ... one launch of the reverse sweep (0: it does not fit),
     int pers_qlM[2] = {0, 0};      // ... one with the insolation table in LDS [tangent] (0: none)
     int bins = 0;                  // 16-lane rows per bin of the binned layout (0: the layout of tmm_persistent.hpp)
@@ -473,6 +480,7 @@ struct tmm_ctx {
     double* ybuf(int i) const { return at<double>(P.o_ybuf[i]); }
     double* vbuf(int i) const { return at<double>(P.o_vbuf[i]); }
     double* part() const { return at<double>(P.o_part); }
+    double* vring() const { return at<double>(P.o_ring + P.rings / 2 * P.ring_bytes); }   // the tangents' half
     // small vectors: 16 rows of vec_stride doubles (per slot, or per slot and parameter)
     double* vec(int row) const { return at<double>(P.o_vec) + (size_t)row * P.vec_stride; }
 
@@ -854,7 +862,7 @@ tmm::Persist persist_args(tmm_ctx* h) {
     ps.abort_flag = h->at<int>(P.o_pabort);
     ps.spin_limit = h->spin_limit;
     ps.ring = h->at<double>(P.o_ring);
-    ps.vring = h->at<double>(P.o_vring);
+    ps.vring = h->vring();
     ps.halo_ptr = h->at<int>(P.o_phaloptr);
     ps.halo_row = h->at<int>(P.o_phalo);
     ps.halo_max = h->pers_hmax;
@@ -912,17 +920,17 @@ tmm::Bins bins_args(const tmm_ctx* h, int M, bool tangent, bool reverse) {
 }
 
 // Ring slot 0 = the initial state, slots 1 .. K-1 the sentinel.
-int init_rings(tmm_ctx* h, int M, size_t ring, tmm::StateView y) {
+int init_rings(tmm_ctx* h, int M, double* rings, tmm::StateView y) {
     const Plan& P = h->P;
     const size_t ring_len = (size_t)tmm::kRing * P.npad * P.ntr;
     if (h->bins) {
         const size_t total = (size_t)tmm::kRingK * P.npad * P.ntr;   // slots 0 .. K-1
         hipLaunchKernelGGL(tmm::k_bins_ring_init, dim3(launch_blocks(total), M), dim3(256), 0, h->stream,
-                           h->at<double>(ring), ring_len, y, P.ntr, P.npad, h->at<int>(P.o_bcell), total);
+                           rings, ring_len, y, P.ntr, P.npad, h->at<int>(P.o_bcell), total);
     } else {
         const size_t total = (size_t)tmm::kRingK * P.n * P.ntr;
         hipLaunchKernelGGL(tmm::k_ring_init, dim3(launch_blocks(total), M), dim3(256), 0, h->stream,
-                           h->at<double>(ring), ring_len, y, P.n, P.ntr, total);
+                           rings, ring_len, y, P.n, P.ntr, total);
     }
     TMM_LAUNCHED();
     return TMM_OK;
@@ -942,7 +950,7 @@ int launch_persistent(tmm_ctx* h, int M, int slot0, tmm::StepRange sr, tmm::Stat
                       tmm::StateView v = {}, tmm::StateView vout = {}) {
     const Plan& P = h->P;
     int rc = reset_flags(h, M);
-    if (rc || (rc = init_rings(h, M, P.o_ring, y)) || (v.p && (rc = init_rings(h, M, P.o_vring, v)))) return rc;
+    if (rc || (rc = init_rings(h, M, h->at<double>(P.o_ring), y)) || (v.p && (rc = init_rings(h, M, h->vring(), v)))) return rc;
     tmm::Grid g = h->grid(h->tilings.front());
     tmm::Model md = h->model();
     tmm::Mats mt = h->mats();
@@ -973,8 +981,9 @@ int launch_persistent(tmm_ctx* h, int M, int slot0, tmm::StepRange sr, tmm::Stat
 int launch_persistent_year(tmm_ctx* h, int nb, const double* y, double* out, const double* v, double* vout) {
     const int W = nb * h->P.ntr;
     tmm::StepRange sr{0, h->P.nstep, nullptr, 1, 0, {}, 0, nullptr, 1};
-    for (int s = 0; s < nb; s += h->pers_M) {
-        const int M = std::min(h->pers_M, nb - s);
+    const int most = h->pers_M[v != nullptr ? 1 : 0];
+    for (int s = 0; s < nb; s += most) {
+        const int M = std::min(most, nb - s);
         const int rc = launch_persistent(h, M, s, sr, batch_view(h, y, W, s), batch_view(h, out, W, s),
                                          batch_view(h, v, W, s), batch_view(h, vout, W, s));
         if (rc) return rc;
@@ -990,7 +999,7 @@ int launch_adjoint_persistent(tmm_ctx* h, int M, int slot0, int j_lo, int j_hi, 
     const Plan& P = h->P;
     // the cotangent uses the forward kernel's ring (launches never overlap)
     int rc = reset_flags(h, M);
-    if (rc || (rc = init_rings(h, M, P.o_ring, mu_in))) return rc;
+    if (rc || (rc = init_rings(h, M, h->at<double>(P.o_ring), mu_in))) return rc;
     tmm::Grid g = h->grid(h->tilings.front());
     tmm::Model md = h->model();
     tmm::Mats mt = h->mats();
@@ -1032,7 +1041,7 @@ bool single_launch(const tmm_ctx* h, int nb, bool derivative) {
     if (h->wide_min_members >= 0 || h->mem_tile > 0) return false;
     const bool members = h->P.ntr <= 2 && h->P.nlayer <= 32 && h->P.ew <= tmm::kMembersEll;
     if (derivative || !members) return true;
-    const int groups = (nb + h->pers_M - 1) / h->pers_M;
+    const int groups = (nb + h->pers_M[0] - 1) / h->pers_M[0];
     return groups <= (h->bins ? 6 + h->P.n / 10000 : 4);
 }
 
@@ -1148,6 +1157,13 @@ int ensure_dyn_lds(const void* fk, size_t dyn) {
     TMM_TRY(hipFuncSetAttribute(fk, hipFuncAttributeMaxDynamicSharedMemorySize, (int)dyn));
     cur = dyn;
     return TMM_OK;
+}
+
+// Members one launch runs side by side where the device holds `resident`
+// copies of the domains: each needs a ring, its tangent another.
+void members_side_by_side(tmm_ctx* h, int resident) {
+    for (int t = 0; t < 2; ++t)
+        h->pers_M[t] = std::max(1, std::min({h->P.side_by_side, resident, t ? h->P.rings / 2 : h->P.rings}));
 }
 
 // Domains that share an explicit-matrix coupling (either direction) with each
@@ -1417,13 +1433,13 @@ int build_bins(tmm_ctx* h, int target_rows, int ncu) {
     TMM_LAUNCHED();
     TMM_TRY(hipStreamSynchronize(h->stream));
     h->pers_G = G;
-    h->pers_M = std::max(1, std::min(P.pers_members, ncu / G));
+    members_side_by_side(h, ncu / G);
     h->pers_tpb = TPB;
     h->pers_hmax = hmax;
     h->pers_ahmax = ahmax;
     h->pers_qmax = std::max(qrows, 0);
-    h->pers_Madj = adj_ok ? h->pers_M : 0;
-    h->pers_qlM[0] = h->pers_qlM[1] = ql ? h->pers_M : 0;
+    h->pers_Madj = adj_ok ? h->pers_M[0] : 0;
+    for (int t = 0; t < 2; ++t) h->pers_qlM[t] = ql ? h->pers_M[t] : 0;
     h->pers_wave_local = true;
     h->pers_ok = true;
     return TMM_OK;
@@ -1445,7 +1461,7 @@ int build_persistent(tmm_ctx* h, int target_rows) {
     h->pers_Madj = 0;
     h->pers_target = target_rows;
     h->bins = 0;
-    if (!coop || !P.o_ring || P.ew > tmm::kEllMax || P.nlayer > 32 || P.neu > tmm::kNeuMax) return TMM_OK;
+    if (!coop || !P.pers_possible) return TMM_OK;
     h->pers_kmax = P.nlayer <= 16 ? 16 : 32;
     if (target_rows < 1) target_rows = kDefaultDomainRows;
     if (P.bins_possible && h->wave_local_enabled && target_rows <= tmm::kBinThreads) {
@@ -1596,12 +1612,12 @@ int build_persistent(tmm_ctx* h, int target_rows) {
     TMM_LAUNCHED();
     TMM_TRY(hipStreamSynchronize(h->stream));
     h->pers_G = G;
-    h->pers_M = std::max(1, std::min(P.pers_members, maxG / G));
+    members_side_by_side(h, maxG / G);
     h->pers_tpb = tpb;
     h->pers_hmax = hmax;
     h->pers_ahmax = ahmax;
     h->pers_qmax = qmax;
-    h->pers_Madj = ahalo_ok ? std::min(h->pers_M, ncu * occ_adj / G) : 0;
+    h->pers_Madj = ahalo_ok ? std::min(h->pers_M[0], ncu * occ_adj / G) : 0;
     h->pers_qlM[0] = ql_members[0];
     h->pers_qlM[1] = ql_members[1];
     h->pers_wave_local = wave_local;
@@ -1656,8 +1672,8 @@ int adjoint_persistent(tmm_ctx* h, int nb, const double* y0, const double* obs, 
     // forward sweep: checkpoints y_{sK} at slot s up to the last segment, whose
     // states y_lo .. y_{nstep-1} go to the segment store; misfit partial sums
     const int lo_last = (nseg - 1) * K;
-    for (int s = 0; s < nb; s += h->pers_M) {
-        const int M = std::min(h->pers_M, nb - s);
+    for (int s = 0; s < nb; s += h->pers_M[0]) {
+        const int M = std::min(h->pers_M[0], nb - s);
         const tmm::StateView ob = batch_view(h, obs, W, s);
         double* ck = ckpt + (size_t)s * ckpt_step;
         tmm::StateView from = batch_view(h, y0, W, s);
@@ -1770,7 +1786,13 @@ int tmm_create(const tmm_desc* d, void* dev_workspace, size_t bytes, void* hip_s
     if (!h) return TMM_ENOMEM;
     int rc = validate(d, h->P);
     if (rc) { delete h; return rc; }
-    if (bytes < h->P.total) { delete h; return TMM_ENOMEM; }
+    if (bytes < h->P.total) {              // with fewer rings, if two are left
+        Plan& P = h->P;
+        const size_t fewer = P.ring_bytes ? (P.total - bytes + P.ring_bytes - 1) / P.ring_bytes : 1;
+        if (fewer + 2 > (size_t)P.rings) { delete h; return TMM_ENOMEM; }
+        P.rings -= (int)fewer;
+        P.total -= fewer * P.ring_bytes;
+    }
     h->stream = static_cast<hipStream_t>(hip_stream);
     h->ws = static_cast<char*>(dev_workspace);
     const Plan& P = h->P;
