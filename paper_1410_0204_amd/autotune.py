@@ -8,7 +8,9 @@ rounding order:
   per workgroup; each domain is one workgroup of up to 256 or 512 rows), and
   the launch-per-step kernels: the streaming one where it runs, and the tile
   kernel with each tile size (32 .. 256 rows per workgroup);
-* ensembles: the member-parallel kernel (one wavefront per water column,
+* ensembles: the library's own choice with several domain sizes (where the
+  single-launch kernels are available it may run groups of members side by
+  side in them), the member-parallel kernel (one wavefront per water column,
   lane = member) with 2, 4 or 8 wavefronts per workgroup and its column order
   (bands of 4 .. 32 latitude rows swept by longitude, or the natural order),
   the tiled member kernel (4 or 8 neighbouring columns per workgroup, each
@@ -71,7 +73,9 @@ def describe(options):
 def candidates(t, nbatch):
     """Option sets to try for this handle and member count (each applied on top of DEFAULTS)."""
     out = []
-    if nbatch == 1 and t.query(T.TMM_Q_PERSISTENT):
+    # (with the default crossover to the member kernel: asking for that kernel by its option rules the
+    # members side by side out)
+    if t.query(T.TMM_Q_PERSISTENT):
         for rows in DOMAIN_ROWS:
             out.append({T.TMM_OPT_PERSISTENT: 1, T.TMM_OPT_DOMAIN_ROWS: rows})
     if nbatch == 1:
