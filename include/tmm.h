@@ -199,8 +199,9 @@ enum {
     TMM_OPT_PERSISTENT = 1,  /* 1 (default): model years run as one persistent cooperative launch
                                 when the grid fits: a single member's always, a batch's in groups of
                                 as many members as fit the device side by side where that is faster
-                                than one launch per step for all of them (few groups; tangents,
-                                gradients and three tracers always) and neither
+                                than one launch per step for all of them (few groups of years with
+                                one or two tracers; of tangents, gradients and three tracers any
+                                number, some kinds fewer without bins) and neither
                                 TMM_OPT_MEMBER_KERNEL_MIN nor TMM_OPT_MEMBER_TILE asks for another
                                 kernel; 0: one launch per step */
     TMM_OPT_DOMAIN_ROWS = 2, /* target rows per workgroup of the persistent kernel (<= 512);

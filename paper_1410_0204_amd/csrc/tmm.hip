@@ -1024,25 +1024,21 @@ int launch_adjoint_persistent(tmm_ctx* h, int M, int slot0, int j_lo, int j_hi, 
     return TMM_OK;
 }
 
-// Whether nb members' model years run through the single-launch kernels, as
-// many members at a time as fit the device, one group after another, instead
-// of one launch per step for the whole batch.  A group's year takes 3.1-3.9 ms
-// (two tracers) whatever the grid; the member kernel's year, at 8 / 32 / 64
-// members, 44 / 60 / 92 ms on the 128x64x15 grid (one member per group), 26 /
-// 33 / 44 ms on 77x39x12 (17000 points, 3 per group) and 22 / 20 / 25 ms on
-// 32x16x8 (2700 points, 21 per group).  The other layout's year is up to twice
-// as long.  Three tracers and derivatives have only the tile kernels besides,
-// whose time grows with the member count (6 members of PO4-DOP-PHY on the
-// 128x64x15 grid 147 ms, a group 5.1 ms).
-bool single_launch(const tmm_ctx* h, int nb, bool derivative) {
+// Whether nb members' model years (or their tangents, or the sweeps of their
+// gradients) run through the single-launch kernels, as many members at a time
+// as fit the device, one group after another, instead of one launch per step
+// for the whole batch (see most_groups).
+bool single_launch(const tmm_ctx* h, int nb, tmm::Sweep sweep) {
+    const Plan& P = h->P;
     if (!h->pers_ok || !h->pers_enabled) return false;
+    const int most = sweep == tmm::kReverse ? h->pers_Madj : h->pers_M[sweep == tmm::kTangent ? 1 : 0];
+    if (most < 1) return false;
     if (nb == 1) return true;
     // a launch-per-step kernel asked for by its options runs
     if (h->wide_min_members >= 0 || h->mem_tile > 0) return false;
-    const bool members = h->P.ntr <= 2 && h->P.nlayer <= 32 && h->P.ew <= tmm::kMembersEll;
-    if (derivative || !members) return true;
-    const int groups = (nb + h->pers_M[0] - 1) / h->pers_M[0];
-    return groups <= (h->bins ? 6 + h->P.n / 10000 : 4);
+    const bool member_kernel = P.ntr <= 2 && P.nlayer <= 32 && P.ew <= tmm::kMembersEll;
+    return (nb + most - 1) / most <= tmm::most_groups(sweep, member_kernel, P.ntr, P.nsub > 1, P.nlayer > 16, 16 * h->bins,
+                                                      P.n);
 }
 
 // After the launches of a call: a set abort flag means a wait of the persistent
@@ -1127,7 +1123,7 @@ int run_year_graph(tmm_ctx* h, int nb, const double* y, double* out, double* a, 
 // step.
 int run_year(tmm_ctx* h, int nb, const double* y, double* out, double* a, double* b,
              const double* v = nullptr, double* vout = nullptr, double* va = nullptr, double* vb = nullptr) {
-    if (single_launch(h, nb, v != nullptr)) return launch_persistent_year(h, nb, y, out, v, vout);
+    if (single_launch(h, nb, v ? tmm::kTangent : tmm::kForward)) return launch_persistent_year(h, nb, y, out, v, vout);
     if (!v && h->graphs_enabled) return run_year_graph(h, nb, y, out, a, b);
     const double* cur = y;
     const double* vcur = v;
@@ -2426,7 +2422,7 @@ int tmm_year_adjoint(tmm_handle h, const double* y0, const double* obs, int ckpt
     const size_t n = P.n, len = n * W;
     const int K = P.ckpt, spm = P.nstep / P.nmat, nseg = P.nstep / K;
     const double dtd = tmm::kDaysPerYear / P.nstep;
-    if (h->pers_Madj > 0 && P.etw <= tmm::kEllMax && single_launch(h, nb, true))
+    if (P.etw <= tmm::kEllMax && single_launch(h, nb, tmm::kReverse))
         return adjoint_persistent(h, nb, y0, obs, J_host, dJdu_host, dJdy0);
     const Tiling& tl = h->tiling_for(W, 1, 256 * 8 * np);
     tmm::Grid g = h->grid(tl);

@@ -34,4 +34,44 @@ constexpr int poll_pause(bool internal_steps, int lanes, int ntr, int workgroups
     return few ? 3 : (lanes == 32 ? base - 3 : base);
 }
 
+// Most groups of members, one launch after another, for which a batch runs
+// through the single-launch kernels instead of one launch per step for all of
+// it.  What a group's year takes hardly depends on the grid; a step's launch
+// takes longer with the points and, unevenly, with the members.
+//
+// Years of one or two tracers have the member kernel besides: its year, at 8 /
+// 32 / 64 members, takes 44 / 60 / 92 ms on the 128x64x15 grid (one member per
+// group), 26 / 33 / 44 ms on 77x39x12 (17000 points, 3 per group) and 22 / 20 /
+// 25 ms on 32x16x8 (2700 points, 21 per group), a group's 3.1-3.9 ms in bins and
+// up to twice that in the packed layout (4 groups 25-33 ms against 41-56).
+//
+// Three tracers, tangents and gradients have the tile kernels besides.  In bins
+// a group is faster up to the widest batches measured (128x64x15, ms, single
+// launches and launch per step: PO4-DOP-PHY years of 64 members 286 and 1057,
+// tangents of 64 348 and 969, gradients of 18 members 234 and 308; one-tracer
+// tangents of 64 251 and 361).  In the packed layout the wide batches of some
+// kinds are not (100x49x23 with 52000 points unless said; `deep`: more than 16
+// layers):
+//   one-tracer tangents 40 members 350 and 423, 64 559 and 450 (128x64x15: 246
+//     and 379, 395 and 360); gradients 25 548 and 505 (128x64x15: 428 and 448)
+//   two-tracer tangents 24 members 441 and 495, 40 695 and 588, with 8 internal
+//     steps 24 members 741 and 665 (128x64x15: 64 members 600 and 966);
+//     gradients 12 members 328 and 348, 18 491 and 365 (128x64x15: 262 and 293,
+//     392 and 309; with 8 internal steps 18 890 and 1079)
+//   three-tracer tangents 4 members 182 and 290, 8 361 and 329, 24 1060 and 598
+//     (with 8 internal steps 1343 and 2431; 128x64x15: 64 members 817 and 2719).
+constexpr int kAnyGroups = 1 << 30;
+enum Sweep { kForward, kTangent, kReverse };
+constexpr int most_groups(Sweep sweep, bool member_kernel, int ntr, bool internal_steps, bool deep, int lanes, int n) {
+    if (sweep == kForward && member_kernel) return lanes > 0 ? 6 + n / 10000 : 4;
+    if (sweep == kForward || lanes > 0) return kAnyGroups;
+    if (sweep == kReverse) {
+        if (internal_steps || ntr == 3) return kAnyGroups;
+        return ntr == 2 ? 13 : (deep ? 22 : kAnyGroups);
+    }
+    if (ntr == 1) return 48;
+    if (!deep) return kAnyGroups;
+    return ntr == 2 ? 20 : (internal_steps ? kAnyGroups : 5);
+}
+
 }  // namespace tmm
