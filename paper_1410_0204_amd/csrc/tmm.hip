@@ -1243,8 +1243,8 @@ std::vector<int> xcd_order(int G) {
 // room that still holds it.  When the next column of the sweep needs a bin
 // more than the domain has, the room left in its bins goes to shallow columns
 // among the next ones of the sweep.  A few band heights are tried, four rows
-// first, until the domains fit the device.  Sets h->bins where everything fits, else leaves
-// the handle to the layout of tmm_persistent.hpp.
+// first, until the domains fit the device.  Sets h->bins where everything
+// fits, else leaves the handle to the layout of tmm_persistent.hpp.
 int build_bins(tmm_ctx* h, int target_rows, int ncu) {
     const Plan& P = h->P;
     const int hb = P.nlayer <= 16 ? 1 : 2, BL = 16 * hb, TPB = tmm::kBinThreads;
@@ -1253,7 +1253,8 @@ int build_bins(tmm_ctx* h, int target_rows, int ncu) {
         std::vector<std::vector<int>> cols, slots;     // per domain: columns and their first lanes
     };
     auto depth = [&](int c) { return P.col_start[c + 1] - P.col_start[c]; };
-    auto fill = [&](int band) {
+    bool table_binds = false;                          // some domain could have held more latitude rows
+    auto fill = [&](int band, bool keep_table) {
         std::vector<int> order(P.ncol);
         for (int c = 0; c < P.ncol; ++c) order[c] = c;
         if (!P.lon.empty())
@@ -1270,10 +1271,12 @@ int build_bins(tmm_ctx* h, int target_rows, int ncu) {
         while (first < P.ncol) {
             std::vector<int> room, cols, slots, lats;
             auto put = [&](int c, bool open) {
-                // a domain (the first one once half full) keeps to the latitude rows its insolation
-                // table holds
+                // a domain keeps to the latitude rows its insolation table holds
                 const bool known = std::find(lats.begin(), lats.end(), P.col_lat[c]) != lats.end();
-                if (!known && lats.size() == tmm::kInsLat && (!out.cols.empty() || 2 * (int)room.size() >= nbin)) return false;
+                if (!known && keep_table && lats.size() == tmm::kInsLat) {
+                    table_binds = true;
+                    return false;
+                }
                 int best = -1;
                 for (int b = 0; b < (int)room.size(); ++b)
                     if (room[b] >= depth(c) && (best < 0 || room[b] < room[best])) best = b;
@@ -1303,16 +1306,29 @@ int build_bins(tmm_ctx* h, int target_rows, int ncu) {
         }
         return out;
     };
+    const size_t most = (size_t)std::min(ncu, kMaxBinDomains);
+    auto fewest = [&](bool keep_table) {
+        Layout lay;
+        for (int band : {4, 3, 5}) {
+            Layout l = fill(band, keep_table);
+            if (lay.cols.empty() || l.cols.size() < lay.cols.size()) lay = std::move(l);
+            if (P.lon.empty() || lay.cols.size() <= most) break;
+        }
+        return lay;
+    };
     Layout lay;
     for (;; ++nbin) {                                  // (larger domains than asked for where they are too many)
-        lay = Layout();
-        for (int band : {4, 3, 5}) {
-            Layout l = fill(band);
-            if (lay.cols.empty() || l.cols.size() < lay.cols.size()) lay = std::move(l);
-            if (P.lon.empty() || (int)lay.cols.size() <= std::min(ncu, kMaxBinDomains)) break;
-        }
-        if ((int)lay.cols.size() <= std::min(ncu, kMaxBinDomains)) break;
-        if (nbin == TPB / BL) return TMM_OK;
+        // a grid that one domain holds is not divided to keep the table: 200 points on 40 latitude rows
+        // take 2.42 ms a year as one domain without it, 2.71 ms as five with it (three tracers 2.74, 3.12)
+        lay = P.n <= nbin * BL ? fill(4, false) : Layout();
+        if (lay.cols.size() == 1) break;
+        lay = fewest(true);
+        if (lay.cols.size() <= most) break;
+        if (nbin < TPB / BL) continue;
+        // the table costs domains: without it a year is 0-6 % longer, in the other layout 50-70 %
+        if (table_binds) lay = fewest(false);
+        if (lay.cols.size() > most) return TMM_OK;
+        break;
     }
     const int G = (int)lay.cols.size();
     std::vector<int> row_dom(P.n), row_lane(P.n), row_cell(P.n, 0), cell_row(P.npad, -1);

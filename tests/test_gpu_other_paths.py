@@ -198,3 +198,19 @@ def test_a_batch_handle_keeps_what_one_member_has(model, rows):
         assert componentwise(np.ravel(J)[b], eJ, "J") <= MISFIT
         assert componentwise(G[b], eG, f"dJ/du {b}") <= ADJOINT
         assert columnwise(_col(dy0, b, ntr), eY, ntr, f"dJ/dy0 {b}") <= ADJOINT
+
+
+@pytest.mark.parametrize("ncol,n,domains", [(60, 200, 1), (150, 520, 2)])
+def test_domains_keep_to_the_latitude_rows_of_their_table(ncol, n, domains):
+    """Many latitude rows: a grid of one domain is left whole and loads its insolation step by step; one of
+    several is divided so that every domain, the first one too, holds its rows' table."""
+    tmm = _tmm()
+    inp = synth.custom(max(2, ncol // 40), 60 if domains > 1 else 40, 4, ncol, n, model=NDOP, nstep=NSTEP)
+    t = tmm.TMM(inp.desc_arrays(), nbatch_max=NB, adjoint_nbatch_max=NB, ckpt_every=48)
+    print(f"[gpu] latitude rows, {t.query(tmm.TMM_Q_DOMAINS)} domains", flush=True)
+    assert t.query(tmm.TMM_Q_BIN_LANES) == 16
+    if domains == 1:
+        assert t.query(tmm.TMM_Q_DOMAINS) == 1 and t.query(tmm.TMM_Q_INSOLATION_LDS) == 0
+    else:
+        assert t.query(tmm.TMM_Q_DOMAINS) > 1 and t.query(tmm.TMM_Q_INSOLATION_LDS) == 1
+    _check(t, inp, oracle.Oracle(inp), f"latitude rows {n}")
