@@ -2273,8 +2273,8 @@ int tmm_set_option(tmm_handle h, int option, int value) {
         case TMM_OPT_DOMAIN_ROWS: {
             if (value < 0) return TMM_EINVAL;
             if (hipStreamSynchronize(h->stream) != hipSuccess) return TMM_EDEVICE;
-            // (the domains of a target depend on nothing that changes: 9 ms for 52749 points)
-            if ((value ? value : kDefaultDomainRows) == (h->pers_target > 0 ? h->pers_target : kDefaultDomainRows)) {
+            // (built domains of a target depend on nothing that changes: 9 ms for 52749 points)
+            if (h->pers_ok && (value ? value : kDefaultDomainRows) == (h->pers_target > 0 ? h->pers_target : kDefaultDomainRows)) {
                 h->pers_target = value;
                 return TMM_OK;
             }
