@@ -38,8 +38,9 @@
 //   forward                5.48 -> 3.62        7.25 -> 5.06    10.1 -> 5.51
 //   with its tangent       8.80 -> 5.52       13.75 -> 9.07    16.7 -> 9.42
 //   misfit and gradient    14.1 -> 9.07        19.0 -> 12.9    33.5 -> 20.0
-// and 8 members' gradients on that grid, which ran the tile kernels before,
-// 224 -> 55; 8 members' years on an irregular 19-layer one 103 -> 28.
+// and 4 members' gradients on that grid, which ran the tile kernels before,
+// 224 -> 52; 9 members' years (one or two each) on an irregular 19-layer one
+// 103 -> 27.
 //
 // The ring keeps the rows in domain order (the lanes of a wavefront store
 // consecutive cells), the tracers of a row side by side: one 16-byte access

@@ -747,7 +747,7 @@ __global__ __launch_bounds__(256) void k_step(Grid g, Model md, Mats mt, int W, 
 // Forward step of one member on grids whose matrices stream from memory (one
 // BGC evaluation per step, at most kStreamLayers layers and kStreamEll
 // explicit entries per row): bound by the bytes of the month pair of Ai and
-// Ae (0.33 GB of the 0.35 GB a step of the 360x180x23 grid moves) on large
+// Ae (0.31 GB of the 0.34 GB a step of the 360x180x23 grid moves) on large
 // grids and by its chain of dependent loads on small ones.  k_step
 // reads the Ai blocks after the barrier that completes z, a few loads at a
 // time per lane; here a workgroup knows its tile's blocks as one contiguous
