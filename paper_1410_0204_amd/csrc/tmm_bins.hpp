@@ -35,9 +35,9 @@
 // wavefront per SIMD, in which every instruction takes at least four cycles:
 // 3.6 ms a year is 1.26 us a step.  A model year, before and after (ms):
 //                         128x64x15 N-DOP     PO4-DOP-PHY   N-DOP, 8 internal
-//   forward                5.48 -> 3.62        7.25 -> 5.06    10.1 -> 5.51
-//   with its tangent       8.80 -> 5.52       13.75 -> 9.07    16.7 -> 9.42
-//   misfit and gradient    14.1 -> 9.07        19.0 -> 12.9    33.5 -> 20.0
+//   forward                5.48 -> 3.54        7.25 -> 4.58    10.1 -> 5.40
+//   with its tangent       8.80 -> 5.51       13.75 -> 8.75    16.7 -> 9.42
+//   misfit and gradient    14.1 -> 8.73        19.0 -> 11.6    33.5 -> 19.6
 // and 4 members' gradients on that grid, which ran the tile kernels before,
 // 224 -> 52; 9 members' years (one or two each) on an irregular 19-layer one
 // 103 -> 27.

@@ -9,10 +9,11 @@ constexpr int kBinThreads = 256;       // lanes per workgroup of the binned kern
 // Halo cells of an LDS buffer of the binned kernels (which holds the own lanes,
 // then the halo) for a largest halo of that many rows: an even number, so that
 // the second buffer starts on 16 bytes with three tracers (24 bytes a cell) as
-// well: its cells are read and written as 16-byte vectors.  Rounded here and
-// not in the kernels: told that the length is even, the compiler spilled a
-// register of k_adjoint_bins<3, true, .> to an accumulation register ahead of
-// the restoring of exec, where only some lanes store it.
+// well: its cells are read and written as 16-byte vectors (8 bytes off, a
+// three-tracer year of the 128x64x15 grid took 5.01 ms instead of 4.56).
+// Rounded here and not in the kernels: told that the length is even, the
+// compiler spilled a register of k_adjoint_bins<3, true, .> to an accumulation
+// register ahead of the restoring of exec, where only some lanes store it.
 constexpr int bins_halo(int rows) { return (rows + 1) / 2 * 2; }
 
 // Pause before the first poll of a step (64-cycle units, see hold_poll), the
@@ -21,9 +22,9 @@ constexpr int bins_halo(int rows) { return (rows + 1) / 2 * 2; }
 // arrive; less in 32-lane bins (twice the product) and in launches of few
 // workgroups (a store is seen sooner).  lanes: 16 or 32 per bin; workgroups:
 // the launch's, over all its members.  Model year on the 128x64x15 grid, ms at
-// 0 / 5 / 7 / 9 / 12: PO4-DOP 4.35 / 3.85 / 3.64 / 3.73 / 3.92, PO4-DOP-PHY
-// 6.30 / 5.62 / 5.28 / 5.10 / 5.18; its tangent year 6.02 / 5.60 / 5.53 / 5.56
-// / 5.67; on the 32x16x8 grid (12 domains) 3.22 at 0, 3.08 at 2, 3.32 at 7.
+// 0 / 5 / 7 / 9 / 12: PO4-DOP 4.27 / 3.66 / 3.53 / 3.66 / 3.87, PO4-DOP-PHY
+// 5.68 / 5.03 / 4.74 / 4.57 / 4.67; the PO4-DOP tangent year 5.99 / 5.56 / 5.52
+// / 5.53 / 5.66; on the 32x16x8 grid (12 domains) 3.18 at 0, 3.04 at 2, 3.26 at 7.
 constexpr int kFewWorkgroups = 64;
 constexpr int poll_pause(bool internal_steps, int lanes, int ntr, int workgroups, bool tangent, bool reverse) {
     if (internal_steps) return 0;
